@@ -6,11 +6,19 @@
 // holds their K/V rows.  The columns of the 16-column MFMA tiles are the
 // consecutive (query position, head) pairs of one KV group, column c being
 // position c / g and head c % g, so every column carries work for any group
-// size g (a position's heads may straddle two workgroups).  A workgroup of kPrefillWaves waves covers kPrefillCols
-// columns of one (sequence, KV head) and streams 32-token K/V blocks, up to
-// its last query position, through a three-stage LDS tile that all its
-// waves share; the blocks are loaded straight into LDS, two blocks ahead of
-// the math.  Per 32 tokens and 16 columns a wave computes
+// size g (a position's heads may straddle two workgroups).  32-token K/V blocks,
+// up to the workgroup's last query position, are loaded straight into LDS.  Two
+// kinds of workgroup, both of kPrefillWaves waves with 48 columns per wave:
+//   * wide (kSplitKv false): its waves cover kPrefillCols = 192 columns of one
+//     (sequence, KV head) and share every block through a three-stage tile,
+//     loaded two blocks ahead of the math;
+//   * narrow (kSplitKv true), for calls with too few columns to fill the chip
+//     with wide ones: all its waves cover the same kSplitCols = 48 columns, each
+//     for a quarter of the blocks through tiles of its own, and their partial
+//     results are merged through LDS in a fixed order.  No workspace, no second
+//     launch.  One request with 301 new tokens over 8,000: 247 us (56 wide
+//     workgroups on 256 CUs, one wave per SIMD) against 65 us.
+// Per 32 tokens and 16 columns a wave computes
 //   S^T = K Q^T                 (8 MFMA 16x16x32, K rows straight from LDS)
 //   causal mask, lazy online softmax
 //   O^T += V^T P^T              (8 MFMA 16x16x32 per bf16 term of P)
@@ -24,6 +32,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <cmath>
 #include <cstdint>
 
@@ -35,18 +44,16 @@ namespace {
 // (sequence, KV head) re-read the same blocks, mostly from L2.
 constexpr int kPrefillLoadAux = 0;
 
-constexpr int kWaitVmcnt0 = 0x0F70;  // s_waitcnt vmcnt(0), expcnt and lgkmcnt left open
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kPrefillWaves = 4;  // waves per workgroup
 constexpr int kPrefillTiles = 3;  // 16-column tiles per wave
 constexpr int kPrefillCols = kPrefillWaves * kPrefillTiles * 16;
-constexpr int kPrefillBlock = 32;  // tokens per LDS stage
-// 16-byte chunks each thread stages per K (and per V) block
-constexpr int kPrefillLoads = kPrefillBlock * 16 / (64 * kPrefillWaves);
-// s_waitcnt vmcnt(N): all but this wave's N most recent loads (one block) have landed
-constexpr int kWaitVmcnt4p = 0x0F70 | (2 * kPrefillLoads);
-static_assert(kPrefillLoads >= 1 && kPrefillLoads * 64 * kPrefillWaves == kPrefillBlock * 16,
-              "the workgroup must tile a block's chunks exactly");
+constexpr int kSplitCols = kPrefillTiles * 16;  // columns of a workgroup whose waves share the tokens out
+constexpr int kPrefillBlock = 32;  // tokens per block
+constexpr int kBlockElems = kPrefillBlock * kHeadDim;
+
+// s_waitcnt vmcnt(n) with expcnt and lgkmcnt left open
+constexpr int wait_vmcnt(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
 struct PrefillPlan {
   int32_t hq;
@@ -62,6 +69,11 @@ struct PrefillPlan {
 // also wait for the loads of later blocks still in flight.  The memory clobber
 // keeps the compiler from moving LDS accesses across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
+
+// 16 bytes per lane from voff in r straight to LDS base + 16 * lane
+__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t r, uint16_t* base, int voff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)base, 16, voff, 0, 0, kPrefillLoadAux);
+}
 
 // Split a pair of non-negative floats into bf16 hi = the value with its low 16
 // bits cleared and bf16 lo = round-to-nearest-even of the exact remainder, so
@@ -81,15 +93,27 @@ __device__ __forceinline__ float max8(float a, float b, float c, float d, float 
   return mx(mx(mx(mx(a, b), c), mx(mx(d, e), f)), mx(g, h));
 }
 
-template <typename OutT, bool kSplitP>
+template <typename OutT, bool kSplitP, bool kSplitKv>
 __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2))) void prefill_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
     const int32_t* __restrict__ offs, const int32_t* __restrict__ lens,
     const int32_t* __restrict__ q_starts, const int32_t* __restrict__ q_lens, PrefillPlan pp,
     OutT* __restrict__ out) {
+  // columns of the workgroup, and the part of it that stages a block together:
+  // the whole workgroup, or each wave for itself
+  constexpr int kTiles = kPrefillTiles;
+  constexpr int kCols = kSplitKv ? kSplitCols : kPrefillCols;
+  constexpr int kStagers = kSplitKv ? 1 : kPrefillWaves;
+  // 16-byte chunks each thread stages per K (and per V) block
+  constexpr int kLoads = kPrefillBlock * 16 / (64 * kStagers);
+  static_assert(kLoads >= 1 && kLoads * 64 * kStagers == kPrefillBlock * 16, "a block's chunks must divide evenly");
+  // all but this wave's newest block of loads have landed
+  constexpr int kWaitBlock = wait_vmcnt(2 * kLoads);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col_wave = kSplitKv ? 0 : wave;    // this wave's columns in the workgroup
+  const int stage_wave = kSplitKv ? 0 : wave;  // its part of the staging
   const int n = lane & 15;
   const int c = lane >> 4;
   const int g = pp.group;
@@ -102,14 +126,14 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const int kv = unit % pp.hkv;
   const int b = unit / pp.hkv;
   const int nq = q_lens[b];
-  // query positions of the workgroup's columns, tile * kPrefillCols onwards
-  const int first_q = tile * kPrefillCols / g;
+  // query positions of the workgroup's columns, tile * kCols onwards
+  const int first_q = tile * kCols / g;
   if (first_q >= nq) return;  // the whole workgroup: nothing to do
   const int seq_len = lens[b];
   const int hist = seq_len - nq;  // position of query 0
   // one past the last column's position; min(q_end, nq) - 1 rather than
   // min(q_end - 1, nq - 1), a form that compiles to 8 more registers
-  const int q_end = (tile * kPrefillCols + kPrefillCols - 1) / g + 1;
+  const int q_end = (tile * kCols + kCols - 1) / g + 1;
   const int last_q = (q_end < nq ? q_end : nq) - 1;
   const int kv_end = hist + last_q + 1;  // tokens any query of the workgroup attends to
   const size_t row_elems = (size_t)pp.hkv * kHeadDim;
@@ -117,12 +141,10 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const uint16_t* kseq = kc + (size_t)offs[b] * row_elems + (size_t)kv * kHeadDim;
   const uint16_t* vseq = vc + (size_t)offs[b] * row_elems + (size_t)kv * kHeadDim;
 
-  __shared__ __attribute__((aligned(16))) uint16_t lds_k0[kPrefillBlock * kHeadDim];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_v0[kPrefillBlock * kHeadDim];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_k1[kPrefillBlock * kHeadDim];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_v1[kPrefillBlock * kHeadDim];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_k2[kPrefillBlock * kHeadDim];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_v2[kPrefillBlock * kHeadDim];
+  // blocks per stage: one shared by the workgroup, or one per wave
+  constexpr int kStageElems = (kSplitKv ? kPrefillWaves : 1) * kBlockElems;
+  __shared__ __attribute__((aligned(16))) uint16_t lds_k0[kStageElems];
+  __shared__ __attribute__((aligned(16))) uint16_t lds_v0[kStageElems];
 
   // logits in log2 units are s * cs with cs >= 0: a negative scale flips the
   // sign of q instead (exact in bf16), so that max(s) * cs = max(s * cs)
@@ -132,11 +154,11 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // this lane's query column in each tile: query index qi, head kv * g + hh,
   // attending to positions 0 .. last_pos (columns past the last query attend
   // to the whole block range and are not written)
-  int qi[kPrefillTiles], hh[kPrefillTiles], last_pos[kPrefillTiles];
-  bf16x8 qb[kPrefillTiles][4];
+  int qi[kTiles], hh[kTiles], last_pos[kTiles];
+  bf16x8 qb[kTiles][4];
 #pragma unroll
-  for (int ct = 0; ct < kPrefillTiles; ++ct) {
-    const int col = tile * kPrefillCols + (wave * kPrefillTiles + ct) * 16 + n;
+  for (int ct = 0; ct < kTiles; ++ct) {
+    const int col = tile * kCols + (col_wave * kTiles + ct) * 16 + n;
     qi[ct] = col / g;
     hh[ct] = col - qi[ct] * g;
     const bool valid = qi[ct] < nq;
@@ -153,23 +175,26 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   }
   // the wave's query positions: tokens at or below mask_from are seen by every
   // column; tokens from wave_end on by none (a wave past the last query idles)
-  const int wave_q0 = (tile * kPrefillCols + wave * kPrefillTiles * 16) / g;
-  const int wave_q1 = (tile * kPrefillCols + (wave + 1) * kPrefillTiles * 16 - 1) / g;
+  const int wave_q0 = (tile * kCols + col_wave * kTiles * 16) / g;
+  const int wave_q1 = (tile * kCols + (col_wave + 1) * kTiles * 16 - 1) / g;
   const bool wave_active = wave_q0 < nq;
   const int mask_from = hist + wave_q0;
   const int wave_end = hist + (wave_q1 < last_q ? wave_q1 : last_q) + 1;
 
-  Softmax st[kPrefillTiles];
-  f32x4 o[kPrefillTiles][8];
+  Softmax st[kTiles];
+  f32x4 o[kTiles][8];
   // lazy-rescale thresholds: the running max plus 2^8, in log2 units (for
   // masked blocks, whose logits are scaled first) and divided by cs (for the
   // raw logits of unmasked blocks); both move only with the running max
-  float thr[kPrefillTiles], thr_raw[kPrefillTiles];
+  float thr[kTiles], thr_raw[kTiles];
 #pragma unroll
-  for (int ct = 0; ct < kPrefillTiles; ++ct) {
+  for (int ct = 0; ct < kTiles; ++ct) {
     thr[ct] = -INFINITY;
     thr_raw[ct] = -INFINITY;
-    st[ct] = Softmax{-INFINITY, 0.f};
+    // A wave that sees only part of the tokens may meet blocks of which a column
+    // sees nothing before any that it does: the lowest finite maximum keeps
+    // 2^(-inf - m) at 0 there (the thresholds still make the first logit count).
+    st[ct] = Softmax{kSplitKv ? -FLT_MAX : -INFINITY, 0.f};
 #pragma unroll
     for (int nb = 0; nb < 8; ++nb) o[ct][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -179,27 +204,19 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // LDS base + 16 L: wave w's round r fills slots 0..15 of tokens
   // 16 r + 4 w + L / 16, so each lane fetches the chunk that the swizzle puts
   // at its slot.  Past kv_end the buffer bound writes zeros.
-  int dvo[kPrefillLoads];
+  int dvo[kLoads];
 #pragma unroll
-  for (int r = 0; r < kPrefillLoads; ++r) {
-    const int t = (tid >> 4) + r * 4 * kPrefillWaves;
+  for (int r = 0; r < kLoads; ++r) {
+    const int t = ((kSplitKv ? lane : tid) >> 4) + r * 4 * kStagers;
     dvo[r] = t * row_bytes + (((tid & 15) ^ tile_swizzle(t)) << 4);
   }
-  auto issue = [&](int tb, uint16_t* dk, uint16_t* dv) {
-    // a block past kv_end gets an empty range: no memory access, zeros in LDS
+  // the resource of the block at tb: past kv_end an empty range (no memory access, zeros in LDS)
+  auto block_rsrc = [&](const uint16_t* seq, int tb) {
     const int rem = kv_end - tb;
     const uint32_t bytes = (uint32_t)((rem <= 0 ? 0 : rem < kPrefillBlock ? rem : kPrefillBlock) * row_bytes);
-    const __amdgpu_buffer_rsrc_t rk = make_rsrc(kseq + (size_t)tb * row_elems, bytes);
-    const __amdgpu_buffer_rsrc_t rv = make_rsrc(vseq + (size_t)tb * row_elems, bytes);
-#pragma unroll
-    for (int r = 0; r < kPrefillLoads; ++r) {
-      const int row0 = r * 4 * kPrefillWaves + 4 * wave;  // first token row of this wave's round
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void*)&dk[row0 * kHeadDim], 16, dvo[r], 0, 0, kPrefillLoadAux);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)&dv[row0 * kHeadDim], 16, dvo[r], 0, 0, kPrefillLoadAux);
-    }
+    return make_rsrc(seq + (size_t)tb * row_elems, bytes);
   };
-  issue(0, lds_k0, lds_v0);
-  issue(kPrefillBlock, lds_k1, lds_v1);
+  auto lds_row = [&](uint16_t* dst, int r) { return dst + (r * 4 * kStagers + 4 * stage_wave) * kHeadDim; };
 
   // per-lane LDS offsets of the operand reads within a 16-token half block
   int k_off[4];
@@ -210,157 +227,306 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const int v_swz = tile_swizzle(v_tok);
   const int v_ch = (n & 3) >> 1;
 
-  // One 32-token block: wait for this wave's loads of it, then the barrier
-  // (every wave's loads have landed, and every wave is done with the stage
-  // read in the previous step); the loads of the block two ahead go into that
-  // stage, in flight for two steps of math.  The three stages are distinct LDS
-  // arrays named at compile time, so the compiler's wait before the reads
-  // covers only this stage's loads.
-  auto step = [&](int t0, const uint16_t* kt, const uint16_t* vt, uint16_t* nk, uint16_t* nv) {
-    // Every step issues the loads of the block two ahead (an empty range past
-    // kv_end), so this wave's loads of this block are all but its newest
-    // block's worth; the barrier then makes everyone's visible.
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt4p);
-    lds_barrier();
-    issue(t0 + 2 * kPrefillBlock, nk, nv);
-    if (wave_active && t0 < wave_end) {
-      // S^T of tokens t0 + 16 h + 4c + i (i < 4) for every column tile
-      f32x4 sc[kPrefillTiles][2];
+  // S^T of a staged block: tokens 16 h + 4c + i (i < 4) for every column tile
+  auto scores = [&](const uint16_t* kt, f32x4 (&sc)[kTiles][2]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        u32x4 kr[4];
+    for (int h = 0; h < 2; ++h) {
+      u32x4 kr[4];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          kr[kk] = *reinterpret_cast<const u32x4*>(kt + 16 * h * kHeadDim + k_off[kk]);
+      for (int kk = 0; kk < 4; ++kk)
+        kr[kk] = *reinterpret_cast<const u32x4*>(kt + 16 * h * kHeadDim + k_off[kk]);
 #pragma unroll
-        for (int ct = 0; ct < kPrefillTiles; ++ct) sc[ct][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int ct = 0; ct < kTiles; ++ct) sc[ct][h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
+      for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-          for (int ct = 0; ct < kPrefillTiles; ++ct)
-            sc[ct][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), qb[ct][kk], sc[ct][h], 0, 0, 0);
-      }
-      const bool masked = t0 + kPrefillBlock - 1 > mask_from;
-      u32x4 phi[kPrefillTiles], plo[kPrefillTiles];
-#pragma unroll
-      for (int ct = 0; ct < kPrefillTiles; ++ct) {
-        float x[8];
-        float lmax;
-        bool grow;
-        if (masked) {  // blocks on the causal diagonal (or past kv_end)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              x[4 * h + i] = (t0 + 16 * h + 4 * c + i > last_pos[ct]) ? -INFINITY : sc[ct][h][i] * cs;
-          lmax = max8(x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]);
-          grow = lmax > thr[ct];
-        } else {
-          const f32x4 a = sc[ct][0], e = sc[ct][1];
-          lmax = max8(a[0], a[1], a[2], a[3], e[0], e[1], e[2], e[3]);
-          grow = lmax > thr_raw[ct];
-        }
-        // lazy rescale: only when some logit exceeds the running max by 2^8;
-        // the column max (across the 4 lanes of a column) only then
-        if (__any(grow)) {
-          if (!masked) lmax *= cs;
-          float mx = fmaxf(lmax, __shfl_xor(lmax, 16));
-          mx = fmaxf(mx, __shfl_xor(mx, 32));
-          const float m_new = fmaxf(st[ct].m, mx);
-          const float alpha = fast_exp2(st[ct].m - m_new);
-          st[ct].l *= alpha;
-#pragma unroll
-          for (int nb = 0; nb < 8; ++nb) o[ct][nb] *= alpha;
-          st[ct].m = m_new;
-          thr[ct] = m_new + kLazyRescale;
-          thr_raw[ct] = thr[ct] / cs;  // +inf for a zero scale: all logits are 0 then
-        }
-        float pr[8];
-        if (masked) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) pr[i] = fast_exp2(x[i] - st[ct].m);
-        } else {
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pr[4 * h + i] = fast_exp2(fmaf(sc[ct][h][i], cs, -st[ct].m));
-        }
-        if (kSplitP) {
-          st[ct].l += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            uint32_t hw, lw;
-            split_bf16x2(pr[2 * j], pr[2 * j + 1], &hw, &lw);
-            phi[ct][j] = hw;
-            plo[ct][j] = lw;
-          }
-        } else {
-          // one bf16 term; the row sum adds the rounded weights the product
-          // uses, a pair per dot product with (1, 1)
-          const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-          float l = st[ct].l;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const bf16x2 pair = {(__bf16)pr[2 * j], (__bf16)pr[2 * j + 1]};  // round to nearest even
-            phi[ct][j] = __builtin_bit_cast(uint32_t, pair);
-            l = __builtin_amdgcn_fdot2_f32_bf16(pair, ones, l, false);
-          }
-          st[ct].l = l;
-        }
-      }
-      // O^T += V^T P^T: the K dimension holds tokens 4c..4c+3 of both halves.
-      // The MFMA stream runs at raised wave priority, so that the other wave
-      // on this SIMD fills the matrix core's issue gaps with its softmax.
-      __builtin_amdgcn_s_setprio(1);
-      // The V^T reads of dimension group nb + 1 are issued before the
-      // products of group nb (the scheduling barrier keeps the compiler from
-      // sinking them to their use), so their latency hides behind those.
-      auto read_vt = [&](int nb, s16x4& v0, s16x4& v1) {
-        const int off = v_row + (((2 * nb + v_ch) ^ v_swz) << 3);
-        v0 = lds_read_tr16(vt + off);
-        v1 = lds_read_tr16(vt + 16 * kHeadDim + off);
-      };
-      s16x4 nv0, nv1;
-      read_vt(0, nv0, nv1);
-#pragma unroll
-      for (int nb = 0; nb < 8; ++nb) {
-        const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(nv0, nv1, 0, 1, 2, 3, 4, 5, 6, 7));
-        if (nb + 1 < 8) read_vt(nb + 1, nv0, nv1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ct = 0; ct < kPrefillTiles; ++ct)
-          o[ct][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, as_bf16x8(phi[ct]), o[ct][nb], 0, 0, 0);
-        if (kSplitP) {
-#pragma unroll
-          for (int ct = 0; ct < kPrefillTiles; ++ct)
-            o[ct][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, as_bf16x8(plo[ct]), o[ct][nb], 0, 0, 0);
-        }
-      }
-      __builtin_amdgcn_s_setprio(0);
+        for (int ct = 0; ct < kTiles; ++ct)
+          sc[ct][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), qb[ct][kk], sc[ct][h], 0, 0, 0);
     }
   };
-  // block j in stage j % 3; step j issues block j + 2 into stage (j + 2) % 3
-  for (int t0 = 0; t0 < kv_end; t0 += 3 * kPrefillBlock) {
-    step(t0, lds_k0, lds_v0, lds_k2, lds_v2);
-    if (t0 + kPrefillBlock >= kv_end) break;
-    step(t0 + kPrefillBlock, lds_k1, lds_v1, lds_k0, lds_v0);
-    if (t0 + 2 * kPrefillBlock >= kv_end) break;
-    step(t0 + 2 * kPrefillBlock, lds_k2, lds_v2, lds_k1, lds_v1);
-  }
-  // no load may land in LDS after the workgroup has released it
-  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  // the online softmax of the block at t0: its logits to weights (one or two bf16 terms)
+  auto weights = [&](int t0, f32x4 (&sc)[kTiles][2], u32x4 (&phi)[kTiles], u32x4 (&plo)[kTiles])
+      __attribute__((always_inline)) {
+    // Blocks on the causal diagonal (or past kv_end) are scaled and masked
+    // first; their logits then count as they are (factor 1, threshold thr),
+    // those of the other blocks with the factor cs (threshold thr_raw).
+    const bool masked = t0 + kPrefillBlock - 1 > mask_from;
+    if (masked) {
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            sc[ct][h][i] = (t0 + 16 * h + 4 * c + i > last_pos[ct]) ? -INFINITY : sc[ct][h][i] * cs;
+    }
+    const float factor = masked ? 1.f : cs;
+    // Lazy rescale: only when some logit exceeds its running max by 2^8; the
+    // column maxima (across the 4 lanes of a column) are taken only then.  One
+    // test and one branch for all tiles: with a branch per tile, and the masked
+    // logits in an array of their own, the compiler moved that array through
+    // registers in every block (burst prefill 10.76 -> 10.28 ms, one wave per SIMD
+    // 247 -> 219 us).  The thresholds are read before the choice between them, a
+    // choice between the arrays would put them in memory.
+    float lm[kTiles];
+    float over = -INFINITY;
+#pragma unroll
+    for (int ct = 0; ct < kTiles; ++ct) {
+      const f32x4 a = sc[ct][0], e = sc[ct][1];
+      lm[ct] = max8(a[0], a[1], a[2], a[3], e[0], e[1], e[2], e[3]);
+      const float t1 = thr[ct], t2 = thr_raw[ct];
+      over = fmaxf(over, lm[ct] - (masked ? t1 : t2));
+    }
+    if (__any(over > 0.f)) {
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct) {
+        const float lmax = lm[ct] * factor;
+        float mx = fmaxf(lmax, __shfl_xor(lmax, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(st[ct].m, mx);
+        const float alpha = fast_exp2(st[ct].m - m_new);
+        st[ct].l *= alpha;
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) o[ct][nb] *= alpha;
+        st[ct].m = m_new;
+        thr[ct] = m_new + kLazyRescale;
+        thr_raw[ct] = thr[ct] / cs;
+      }
+    }
+#pragma unroll
+    for (int ct = 0; ct < kTiles; ++ct) {
+      float pr[8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pr[4 * h + i] = fast_exp2(fmaf(sc[ct][h][i], factor, -st[ct].m));
+      if (kSplitP) {
+        st[ct].l += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          uint32_t hw, lw;
+          split_bf16x2(pr[2 * j], pr[2 * j + 1], &hw, &lw);
+          phi[ct][j] = hw;
+          plo[ct][j] = lw;
+        }
+      } else {
+        // one bf16 term; the row sum adds the rounded weights the product
+        // uses, a pair per dot product with (1, 1)
+        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+        float l = st[ct].l;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bf16x2 pair = {(__bf16)pr[2 * j], (__bf16)pr[2 * j + 1]};  // round to nearest even
+          phi[ct][j] = __builtin_bit_cast(uint32_t, pair);
+          l = __builtin_amdgcn_fdot2_f32_bf16(pair, ones, l, false);
+        }
+        st[ct].l = l;
+      }
+    }
+  };
+  auto values = [&](const uint16_t* vt, const u32x4 (&phi)[kTiles], const u32x4 (&plo)[kTiles])
+      __attribute__((always_inline)) {
+    // O^T += V^T P^T: the K dimension holds tokens 4c..4c+3 of both halves.
+    // The MFMA stream runs at raised wave priority, so that the other wave
+    // on this SIMD fills the matrix core's issue gaps with its softmax.
+    __builtin_amdgcn_s_setprio(1);
+    // The V^T reads of dimension group nb + 1 are issued before the
+    // products of group nb (the scheduling barrier keeps the compiler from
+    // sinking them to their use), so their latency hides behind those.
+    auto read_vt = [&](int nb, s16x4& v0, s16x4& v1) {
+      const int off = v_row + (((2 * nb + v_ch) ^ v_swz) << 3);
+      v0 = lds_read_tr16(vt + off);
+      v1 = lds_read_tr16(vt + 16 * kHeadDim + off);
+    };
+    s16x4 nv0, nv1;
+    read_vt(0, nv0, nv1);
+#pragma unroll
+    for (int nb = 0; nb < 8; ++nb) {
+      const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(nv0, nv1, 0, 1, 2, 3, 4, 5, 6, 7));
+      if (nb + 1 < 8) read_vt(nb + 1, nv0, nv1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct)
+        o[ct][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, as_bf16x8(phi[ct]), o[ct][nb], 0, 0, 0);
+      if (kSplitP) {
+#pragma unroll
+        for (int ct = 0; ct < kTiles; ++ct)
+          o[ct][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, as_bf16x8(plo[ct]), o[ct][nb], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+  if constexpr (!kSplitKv) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds_k1[kStageElems];
+    __shared__ __attribute__((aligned(16))) uint16_t lds_v1[kStageElems];
+    __shared__ __attribute__((aligned(16))) uint16_t lds_k2[kStageElems];
+    __shared__ __attribute__((aligned(16))) uint16_t lds_v2[kStageElems];
+    auto issue = [&](int tb, uint16_t* dk, uint16_t* dv) {
+      const __amdgpu_buffer_rsrc_t rk = block_rsrc(kseq, tb), rv = block_rsrc(vseq, tb);
+#pragma unroll
+      for (int r = 0; r < kLoads; ++r) {
+        load16_to_lds(rk, lds_row(dk, r), dvo[r]);
+        load16_to_lds(rv, lds_row(dv, r), dvo[r]);
+      }
+    };
+    // One 32-token block: wait for this wave's loads of it, then the barrier
+    // (every wave's loads have landed, and every wave is done with the stage
+    // read in the previous step); the loads of the block two ahead go into that
+    // stage, in flight for two steps of math.  The three stages are distinct LDS
+    // arrays named at compile time, so the compiler's wait before the reads
+    // covers only this stage's loads.
+    auto step = [&](int t0, const uint16_t* kt, const uint16_t* vt, uint16_t* nk, uint16_t* nv) __attribute__((always_inline)) {
+      // Every step issues the loads of the block two ahead (an empty range past
+      // kv_end), so this wave's loads of this block are all but its newest
+      // block's worth; the barrier then makes everyone's visible.
+      __builtin_amdgcn_s_waitcnt(kWaitBlock);
+      lds_barrier();
+      issue(t0 + 2 * kPrefillBlock, nk, nv);
+      if (wave_active && t0 < wave_end) {
+        f32x4 sc[kTiles][2];
+        u32x4 phi[kTiles], plo[kTiles];
+        scores(kt, sc);
+        weights(t0, sc, phi, plo);
+        values(vt, phi, plo);
+      }
+    };
+    issue(0, lds_k0, lds_v0);
+    issue(kPrefillBlock, lds_k1, lds_v1);
+    // block j in stage j % 3; step j issues block j + 2 into stage (j + 2) % 3
+    for (int t0 = 0; t0 < kv_end; t0 += 3 * kPrefillBlock) {
+      step(t0, lds_k0, lds_v0, lds_k2, lds_v2);
+      step(t0 + kPrefillBlock, lds_k1, lds_v1, lds_k0, lds_v0);
+      step(t0 + 2 * kPrefillBlock, lds_k2, lds_v2, lds_k1, lds_v1);
+    }
+    // no load may land in LDS after the workgroup has released it
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
 
 #pragma unroll
-  for (int ct = 0; ct < kPrefillTiles; ++ct) {
-    float l_tot = st[ct].l + __shfl_xor(st[ct].l, 16);
-    l_tot += __shfl_xor(l_tot, 32);
-    if (qi[ct] < nq) {
-      const float inv = 1.0f / l_tot;
-      OutT* orow = out + ((size_t)(q_starts[b] + qi[ct]) * pp.hq + (size_t)kv * g + hh[ct]) * kHeadDim + 4 * c;
+    for (int ct = 0; ct < kTiles; ++ct) {
+      float l_tot = st[ct].l + __shfl_xor(st[ct].l, 16);
+      l_tot += __shfl_xor(l_tot, 32);
+      if (qi[ct] < nq) {
+        const float inv = 1.0f / l_tot;
+        OutT* orow = out + ((size_t)(q_starts[b] + qi[ct]) * pp.hq + (size_t)kv * g + hh[ct]) * kHeadDim + 4 * c;
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) store4<OutT>(orow + 16 * nb, o[ct][nb] * inv);
+        for (int nb = 0; nb < 8; ++nb) store4<OutT>(orow + 16 * nb, o[ct][nb] * inv);
+      }
+    }
+  } else {
+    // Wave w takes blocks w, w + 4, w + 8, ... of the workgroup's token range
+    // through its own K and V tiles, with no barrier.  A tile is refilled with
+    // the wave's next block as soon as it has been read: K while the softmax and
+    // P.V run, V while the next block's K Q^T and softmax do.
+    constexpr int kStride = kPrefillWaves * kPrefillBlock;
+    uint16_t* const kt = lds_k0 + wave * kBlockElems;
+    uint16_t* const vt = lds_v0 + wave * kBlockElems;
+    auto issue = [&](const uint16_t* seq, int tb, uint16_t* dst) {
+      const __amdgpu_buffer_rsrc_t rs = block_rsrc(seq, tb);
+#pragma unroll
+      for (int r = 0; r < kLoads; ++r) load16_to_lds(rs, lds_row(dst, r), dvo[r]);
+    };
+    issue(kseq, wave * kPrefillBlock, kt);
+    issue(vseq, wave * kPrefillBlock, vt);
+    // every query of the workgroup is a column of every wave, so no block below
+    // kv_end is without work
+    for (int t0 = wave * kPrefillBlock; t0 < kv_end; t0 += kStride) {
+      f32x4 sc[kTiles][2];
+      u32x4 phi[kTiles], plo[kTiles];
+      __builtin_amdgcn_s_waitcnt(wait_vmcnt(kLoads));  // this block's K; its V is still on the way
+      asm volatile("" ::: "memory");
+      scores(kt, sc);
+      // the tile's reads have returned before its refill is issued
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      issue(kseq, t0 + kStride, kt);
+      weights(t0, sc, phi, plo);
+      __builtin_amdgcn_s_waitcnt(wait_vmcnt(kLoads));  // this block's V
+      asm volatile("" ::: "memory");
+      values(vt, phi, plo);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      issue(vseq, t0 + kStride, vt);
+    }
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+    __syncthreads();  // the tiles now take the waves' partial results
+
+    // Merge of the waves' partial results, one half of the dimensions at a time:
+    // wave w puts its columns' (max, sum) pairs and unnormalised outputs into its
+    // part of the tiles, 16-byte chunk ch of column j at slot ch ^ (j & 15)
+    // (conflict-free writes), and every thread adds up 4 dimensions of some columns.
+    constexpr int kHalf = kHeadDim / 2;
+    constexpr int kChunks = kHalf / 4;
+    constexpr int kPartFloats = kCols * kHalf;  // then the (max, sum) pairs
+    static_assert(kPartFloats * 4 + kCols * (int)sizeof(float2) <= 2 * kBlockElems * 2,
+                  "a wave's partial results must fit half of a tile array");
+    auto part_of = [&](int w) {
+      return reinterpret_cast<float*>((w < 2 ? lds_k0 : lds_v0) + (w & 1) * 2 * kBlockElems);
+    };
+    float* const mine = part_of(wave);
+#pragma unroll
+    for (int ct = 0; ct < kTiles; ++ct) {
+      float l_tot = st[ct].l + __shfl_xor(st[ct].l, 16);
+      l_tot += __shfl_xor(l_tot, 32);
+      if (c == 0) reinterpret_cast<float2*>(mine + kPartFloats)[ct * 16 + n] = make_float2(st[ct].m, l_tot);
+    }
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half > 0) __syncthreads();  // the first half has been read
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          *reinterpret_cast<f32x4*>(mine + (ct * 16 + n) * kHalf + (((4 * nb + c) ^ n) << 2)) = o[ct][4 * half + nb];
+      __syncthreads();
+      const int ch = tid % kChunks;
+#pragma unroll
+      for (int j = tid / kChunks; j < kCols; j += 64 * kPrefillWaves / kChunks) {
+        const int col = tile * kCols + j;
+        const int q_idx = col / g;
+        if (q_idx >= nq) continue;
+        float2 ml[kPrefillWaves];
+        float m = -FLT_MAX;
+#pragma unroll
+        for (int w = 0; w < kPrefillWaves; ++w) {
+          ml[w] = reinterpret_cast<const float2*>(part_of(w) + kPartFloats)[j];
+          m = fmaxf(m, ml[w].x);
+        }
+        float l = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kPrefillWaves; ++w) {
+          const float wt = fast_exp2(ml[w].x - m);
+          l += wt * ml[w].y;
+          acc += wt * *reinterpret_cast<const f32x4*>(part_of(w) + j * kHalf + ((ch ^ (j & 15)) << 2));
+        }
+        const float inv = 1.0f / l;
+        OutT* orow = out + ((size_t)(q_starts[b] + q_idx) * pp.hq + (size_t)kv * g + (col - q_idx * g)) * kHeadDim;
+        store4<OutT>(orow + half * kHalf + 4 * ch, acc * inv);
+      }
     }
   }
+}
+
+struct PrefillArgs {
+  const uint16_t *q, *kc, *vc;
+  const int32_t *offs, *lens, *q_starts, *q_lens;
+  PrefillPlan plan;
+  void* out;
+  unsigned grid;
+  hipStream_t stream;
+};
+
+template <typename OutT, bool kSplitP, bool kSplitKv>
+void launch_one(const PrefillArgs& a) {
+  hipLaunchKernelGGL((prefill_kernel<OutT, kSplitP, kSplitKv>), dim3(a.grid), dim3(64 * kPrefillWaves), 0,
+                     a.stream, a.q, a.kc, a.vc, a.offs, a.lens, a.q_starts, a.q_lens, a.plan,
+                     static_cast<OutT*>(a.out));
+}
+
+template <typename OutT, bool kSplitP>
+void launch_prefill(const PrefillArgs& a, bool split_kv) {
+  if (split_kv)
+    launch_one<OutT, kSplitP, true>(a);
+  else
+    launch_one<OutT, kSplitP, false>(a);
 }
 
 }  // namespace
@@ -387,34 +553,29 @@ extern "C" int ctx_prefill_attn_run(ctx_decode_attn* h, const void* q, const voi
   pp.hq = d.num_q_heads;
   pp.hkv = d.num_kv_heads;
   pp.group = g;
-  pp.tiles = (int32_t)(((int64_t)max_q_len * g + kPrefillCols - 1) / kPrefillCols);
   pp.scale_log2 = (float)((double)scale * 1.4426950408889634);
   pp.units = num_seqs * d.num_kv_heads;
-  const int64_t blocks = round_up(pp.units, kXcds) * pp.tiles;  // units padded to whole XCD rounds
-  if (blocks > INT32_MAX) return fail(CTX_ERR_INVALID_ARG, "prefill grid too large");
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const uint16_t* qp = static_cast<const uint16_t*>(q);
-  const uint16_t* kp = static_cast<const uint16_t*>(k_cache);
-  const uint16_t* vp = static_cast<const uint16_t*>(v_cache);
-  const dim3 grid((unsigned)blocks), block(64 * kPrefillWaves);
+  const int64_t cols = (int64_t)max_q_len * g;
+  const int64_t units = round_up(pp.units, kXcds);  // padded to whole XCD rounds
+  const int64_t whole = units * ((cols + kPrefillCols - 1) / kPrefillCols);
+  // A CU holds two workgroups of either kind.  Where the wide ones would not
+  // fill the chip even once, the narrow ones (4 times as many, each through a
+  // quarter of the tokens) do: one request with 301 new tokens over 8,000 (56
+  // wide workgroups) 219 -> 65 us, 8 requests (448, two-term weights) 255 -> 219;
+  // with more they lose, since they read every K/V block 4 times as often: 16
+  // requests (1,408) 631 against 733 us, 64 requests 2,806 against 3,244.
+  const bool split_kv = whole <= 2 * (int64_t)h->num_cus;
+  const int64_t blocks = split_kv ? units * ((cols + kSplitCols - 1) / kSplitCols) : whole;
+  pp.tiles = (int32_t)(blocks / units);
+  if (whole > INT32_MAX) return fail(CTX_ERR_INVALID_ARG, "prefill grid too large");
+  const PrefillArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
+                      static_cast<const uint16_t*>(v_cache), seq_offsets, seq_lens, q_starts, q_lens, pp, out,
+                      (unsigned)blocks, reinterpret_cast<hipStream_t>(stream)};
   const bool split_p = (flags & CTX_PREFILL_SPLIT_P) != 0;
-  if (d.out_dtype == CTX_DTYPE_F32) {
-    float* op = static_cast<float*>(out);
-    if (split_p)
-      hipLaunchKernelGGL((prefill_kernel<float, true>), grid, block, 0, s, qp, kp, vp, seq_offsets, seq_lens,
-                         q_starts, q_lens, pp, op);
-    else
-      hipLaunchKernelGGL((prefill_kernel<float, false>), grid, block, 0, s, qp, kp, vp, seq_offsets, seq_lens,
-                         q_starts, q_lens, pp, op);
-  } else {
-    uint16_t* op = static_cast<uint16_t*>(out);
-    if (split_p)
-      hipLaunchKernelGGL((prefill_kernel<uint16_t, true>), grid, block, 0, s, qp, kp, vp, seq_offsets, seq_lens,
-                         q_starts, q_lens, pp, op);
-    else
-      hipLaunchKernelGGL((prefill_kernel<uint16_t, false>), grid, block, 0, s, qp, kp, vp, seq_offsets,
-                         seq_lens, q_starts, q_lens, pp, op);
-  }
+  if (d.out_dtype == CTX_DTYPE_F32)
+    split_p ? launch_prefill<float, true>(a, split_kv) : launch_prefill<float, false>(a, split_kv);
+  else
+    split_p ? launch_prefill<uint16_t, true>(a, split_kv) : launch_prefill<uint16_t, false>(a, split_kv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return CTX_OK;

@@ -129,6 +129,39 @@ def test_prefill_last_row_equals_decode():
     assert_parity(got[last], dec, "bf16 weights against the decode kernel", tight=False)
 
 
+@pytest.mark.parametrize("split_p", MODES)
+@pytest.mark.parametrize("hq,hkv,hist", [(32, 8, (0, 0)), (32, 8, (0, 300)), (16, 8, (120, 140)), (14, 2, (1, 400)),
+                                         (16, 1, (31, 33))])
+def test_prefill_narrow_and_wide_workgroups(hq, hkv, hist, split_p):
+    """The same queries through both kinds of workgroup: max_q_len sizes the
+    grid, and a generous bound takes the call past the size up to which the
+    narrow ones (48 columns, the tokens shared out over the waves) are used.
+    Query counts around the edges of both tiles (48 and 192 columns), token
+    counts that leave some waves of a narrow workgroup without a block, and
+    unequal keys (the waves' running maxima differ)."""
+    g = hq // hkv
+    new = sorted({max(1, c // g + d) for c in (16, 48, 192) for d in (-1, 0, 1)})
+    w, lay, lens, nq, qs, q, k, v = prefill_case(hq + hist[1], hq, hkv, batch=len(new), hist=hist, new=(1, 1),
+                                                 peaky=True)
+    rng = np.random.default_rng(hq)
+    hists = rng.integers(hist[0], hist[1] + 1, size=len(new))
+    nq = np.array(new, np.int32)
+    lens = (hists + nq).astype(np.int32)
+    lay = wl.make_layout(lens, 1, gap_max=5, shuffle=True, rng=rng)
+    k, v = wl.layer_kv_bits(w, lay, 0, fill=wl.BF16_NAN)
+    qs = np.concatenate([[0], np.cumsum(nq)[:-1]]).astype(np.int32)
+    q = rand_bits(rng, (int(nq.sum()), hq, 128))
+    ref = oracle.prefill_attn(q, k, v, lay.offsets, lens, qs, nq, w.scale)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for bound in (int(nq.max()), 192 * 2 * cus + 1):  # one KV head and one sequence already exceed 2 workgroups per CU
+        with DecodeAttention(hq, hkv, len(lens), int(lens.max())) as attn:
+            out = torch.full(q.shape, -555.0, dtype=torch.float32, device=dev())
+            attn.prefill(up_bf16(q), up_bf16(k), up_bf16(v), up_i32(lay.offsets), up_i32(lens), up_i32(qs),
+                         up_i32(nq), bound, w.scale, out, split_p=split_p)
+            torch.cuda.synchronize()
+        assert_parity(out.cpu().numpy(), ref, f"{hq}/{hkv} max_q_len {bound} split_p={split_p}", tight=split_p)
+
+
 def test_prefill_abi():
     lib = bd.load_library()
     with DecodeAttention(32, 8, 2, 32) as attn:
