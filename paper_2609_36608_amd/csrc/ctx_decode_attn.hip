@@ -51,8 +51,14 @@ namespace {
 
 constexpr int kBlock = 16;        // tokens per MFMA block
 constexpr int kMaxGroup = 16;     // query heads per KV head (MFMA N dimension)
-constexpr int kMinRange = 64;     // smallest balanced range, tokens
-constexpr int kMergeWaves = 4;
+// Smallest balanced range, tokens.  A short call is bound by its chain of
+// dependent loads, so one block per wave beats fewer, longer ranges (same merge
+// for all three): a step of 28 layers over 4 contexts of 256..1024 tokens 399,
+// 419 and 472 us with 16, 32 and 64; one context of 1,000 tokens 11.2, 12.2 and
+// 13.9 us.  Larger batches have longer ranges anyway.
+constexpr int kMinRange = 16;
+// waves of a merge workgroup in which seg_waves waves share a head's segments
+constexpr int merge_waves(int seg_waves) { return seg_waves < 4 ? 4 : seg_waves; }
 constexpr int kWgWaves = 8;  // most waves (KV heads of one range) per split workgroup
 constexpr int kTileBytes = 2 * kBlock * kHeadDim * 2;  // one wave's K and V tiles in LDS
 // Waves per SIMD the split kernel is compiled for: 3 for contiguous caches
@@ -86,11 +92,33 @@ struct Paged {
 
 // ------------------------------------------------------------ wave helpers
 
-__device__ __forceinline__ int64_t wave_sum(int64_t x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+// x of the lane that a data-parallel-primitive control word names, 0 where it names none
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int64_t dpp_or_zero(int64_t x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRowMask, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), kCtrl, kRowMask, 0xf, false);
+  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// Inclusive prefix sum over the wave: rows of 16 lanes by shifts of 1, 2, 4 and
+// 8, then each row's total to the rows after it.
+__device__ __forceinline__ int64_t wave_scan(int64_t x) {
+  x += dpp_or_zero<0x111, 0xf>(x);
+  x += dpp_or_zero<0x112, 0xf>(x);
+  x += dpp_or_zero<0x114, 0xf>(x);
+  x += dpp_or_zero<0x118, 0xf>(x);
+  x += dpp_or_zero<0x142, 0xa>(x);  // lane 15 of rows 0 and 2 to rows 1 and 3
+  x += dpp_or_zero<0x143, 0xc>(x);  // lane 31 to rows 2 and 3
   return x;
 }
+
+__device__ __forceinline__ int64_t lane_value(int64_t x, int src) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)x, src);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(x >> 32), src);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ int64_t wave_sum(int64_t x) { return lane_value(wave_scan(x), 63); }
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
@@ -150,13 +178,7 @@ __device__ __forceinline__ LaneScan scan_lane_lens(const int32_t* __restrict__ l
                                                    int pad) {
   LaneScan r;
   r.len = lane < n ? padded(lens[lane], pad) : 0;
-  int64_t incl = r.len;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int64_t y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
-  r.incl = incl;
+  r.incl = wave_scan(r.len);
   return r;
 }
 
@@ -267,13 +289,13 @@ __global__ __launch_bounds__(64 * kWgWaves) __attribute__((amdgpu_waves_per_eu(k
   int b;
   if (p.num_seqs <= 64) {
     const LaneScan sc = scan_lane_lens(lens, p.num_seqs, lane, p.pad);
-    total = __shfl(sc.incl, 63);
+    total = lane_value(sc.incl, 63);
     width = range_width(total, p);
     ws = (int64_t)w * width;
     if (ws >= total) return;
     const unsigned long long hit = __ballot(sc.incl - sc.len <= ws && ws < sc.incl);
     b = __ffsll(hit) - 1;
-    pos = __shfl(sc.incl - sc.len, b);
+    pos = lane_value(sc.incl - sc.len, b);
   } else {
     total = sum_lens(lens, p.num_seqs, lane, p.pad);
     width = range_width(total, p);
@@ -454,96 +476,122 @@ __global__ __launch_bounds__(64 * kWgWaves) __attribute__((amdgpu_waves_per_eu(k
 
 // ------------------------------------------------------------ merge kernel
 
-__device__ __forceinline__ float lane_value(float x, int src) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src));
-}
+// Bound by latency: the partials are a few MB, and a kernel with one wave per
+// head read them in a chain (19.8 us for one sequence's 256 segments), or, at
+// 194 registers, in four rounds of workgroups (22 us for 256 sequences).
+// One (sequence, query head) is merged by kSegWaves waves, each taking a run of
+// its segments, combined through LDS in wave order.  A wave reads two segments
+// at a time: half h of its lanes owns segments of parity h, lane l of the half
+// dims 4l .. 4l + 3.  The segments' weights are computed one per lane and read
+// from there; kMergeBatch pairs of partial outputs are in flight at once.
+constexpr int kMergeBatch = 8;
 
-// One wave per (sequence, query head); lane l owns dims 2l, 2l+1.  Segment
-// weights are computed one segment per lane; partial outputs are read in
-// batches of kMergeBatch segments, the next batch in flight while the current
-// one is accumulated.
-constexpr int kMergeBatch = 16;
-
-__device__ __forceinline__ void load_partials(float2 (&dst)[kMergeBatch], const float* __restrict__ o_ws,
-                                              size_t first, size_t stride, int s0, int cnt, int lane) {
-#pragma unroll
-  for (int u = 0; u < kMergeBatch; ++u)
-    dst[u] = s0 + u < cnt
-                 ? reinterpret_cast<const float2*>(o_ws + (first + (size_t)(s0 + u) * stride) * kHeadDim)[lane]
-                 : make_float2(0.f, 0.f);
-}
-
-template <typename OutT>
-__global__ __launch_bounds__(64 * kMergeWaves) void decode_merge_kernel(
+template <typename OutT, int kSegWaves>
+__global__ __launch_bounds__(64 * merge_waves(kSegWaves)) void decode_merge_kernel(
     const int32_t* __restrict__ lens, Plan p, const float* __restrict__ o_ws,
     const float2* __restrict__ ml_ws, OutT* __restrict__ out) {
+  constexpr int kHeads = merge_waves(kSegWaves) / kSegWaves;  // per workgroup
   const int lane = threadIdx.x & 63;
-  const int gw = blockIdx.x * kMergeWaves + (threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int sw = wave % kSegWaves;
+  const int gw = blockIdx.x * kHeads + wave / kSegWaves;
   if (gw >= p.num_seqs * p.hq) return;
   const int b = gw / p.hq;
   const int h = gw - b * p.hq;
   const int kv = h / p.group;
   const int qi = h - kv * p.group;
-  int64_t seq_len, total, pos;
-  seq_len = lens[b];
+  const int64_t seq_len = lens[b];
+  int64_t total, pos;
   if (p.num_seqs <= 64) {
     const LaneScan sc = scan_lane_lens(lens, p.num_seqs, lane, p.pad);
-    total = __shfl(sc.incl, 63);
-    pos = __shfl(sc.incl - sc.len, b);
+    total = lane_value(sc.incl, 63);
+    pos = lane_value(sc.incl - sc.len, b);
   } else {
-    total = sum_lens(lens, p.num_seqs, lane, p.pad);
-    pos = sum_lens(lens, b, lane, p.pad);
-  }
-  float r0 = 0.f, r1 = 0.f;
-  if (seq_len > 0) {
-    const int64_t width = range_width(total, p);
-    const int64_t wf = pos / width;
-    int64_t wl = (pos + seq_len - 1) / width;
-    if (wf == wl) return;  // written by the split kernel
-    // only reachable when seq_lens breaks the max_seq_len contract: stay in the workspace
-    if (wl >= p.num_ranges) wl = p.num_ranges - 1;
-    const int nseg = (int)(wl - wf + 1);
-    // partial (m, l, o) of segment j lives at slot wf + j + b
-    const size_t first = ((size_t)(wf + b) * p.hkv + kv) * p.group + qi;
-    const size_t stride = (size_t)p.hkv * p.group;
-    float2 cur[kMergeBatch];
-    load_partials(cur, o_ws, first, stride, 0, nseg < 64 ? nseg : 64, lane);
-    const float2 ml0 = lane < nseg ? ml_ws[first + (size_t)lane * stride] : make_float2(-INFINITY, 0.f);
-    float m = ml0.x;
-    for (int j = lane + 64; j < nseg; j += 64) m = fmaxf(m, ml_ws[first + (size_t)j * stride].x);
-    m = wave_max(m);
-    float lsum = 0.f;
-    for (int base = 0; base < nseg; base += 64) {
-      const int cnt = nseg - base < 64 ? nseg - base : 64;
-      const float2 ml = base == 0 ? ml0
-                                  : (lane < cnt ? ml_ws[first + (size_t)(base + lane) * stride]
-                                                : make_float2(-INFINITY, 0.f));
-      const float wj = lane < cnt ? fast_exp2(ml.x - m) : 0.f;
-      lsum += wj * ml.y;
-      if (base > 0) load_partials(cur, o_ws, first + (size_t)base * stride, stride, 0, cnt, lane);
-      for (int s0 = 0; s0 < cnt; s0 += kMergeBatch) {
-        float2 nxt[kMergeBatch];
-        const bool more = s0 + kMergeBatch < cnt;
-        if (more) load_partials(nxt, o_ws, first + (size_t)base * stride, stride, s0 + kMergeBatch, cnt, lane);
-#pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-          const float wgt = lane_value(wj, (s0 + u) & 63);
-          r0 += wgt * cur[u].x;
-          r1 += wgt * cur[u].y;
-        }
-        if (more) {
-#pragma unroll
-          for (int u = 0; u < kMergeBatch; ++u) cur[u] = nxt[u];
-        }
-      }
+    total = 0;
+    pos = 0;
+    for (int i = lane; i < p.num_seqs; i += 64) {
+      const int64_t len = padded(lens[i], p.pad);
+      total += len;
+      if (i < b) pos += len;
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-    const float inv = 1.0f / lsum;
-    r0 *= inv;
-    r1 *= inv;
+    total = wave_sum(total);
+    pos = wave_sum(pos);
   }
-  store2<OutT>(out + ((size_t)b * p.hq + h) * kHeadDim + 2 * lane, r0, r1);
+  const int half = lane >> 5;
+  const int d = (lane & 31) * 4;
+  OutT* orow = out + ((size_t)b * p.hq + h) * kHeadDim + d;
+  if (seq_len <= 0) {
+    if (sw == 0 && half == 0) store4<OutT>(orow, f32x4{0.f, 0.f, 0.f, 0.f});
+    return;
+  }
+  const int64_t width = range_width(total, p);
+  const int64_t wf = pos / width;
+  int64_t wl = (pos + seq_len - 1) / width;
+  if (wf == wl) return;  // written by the split kernel
+  // only reachable when seq_lens breaks the max_seq_len contract: stay in the workspace
+  if (wl >= p.num_ranges) wl = p.num_ranges - 1;
+  const int nseg = (int)(wl - wf + 1);
+  // partial (m, l, o) of segment j lives at slot wf + j + b
+  const size_t first = ((size_t)(wf + b) * p.hkv + kv) * p.group + qi;
+  const size_t stride = (size_t)p.hkv * p.group;
+  const int per_wave = (nseg + kSegWaves - 1) / kSegWaves;
+  const int j0 = sw * per_wave;
+  const int j1 = j0 + per_wave < nseg ? j0 + per_wave : nseg;
+
+  float m = -INFINITY, lsum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const float* o_first = o_ws + first * kHeadDim + d;
+  f32x4 part[kMergeBatch];
+  auto load_parts = [&](int j) {
+#pragma unroll
+    for (int u = 0; u < kMergeBatch; ++u) {
+      const int ju = j + 2 * u + half;
+      part[u] = ju < j1 ? *reinterpret_cast<const f32x4*>(o_first + (size_t)ju * stride * kHeadDim)
+                        : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  if (j0 < j1) load_parts(j0);
+  const float2 ml0 = j0 + lane < j1 ? ml_ws[first + (size_t)(j0 + lane) * stride] : make_float2(-INFINITY, 0.f);
+  m = ml0.x;
+  for (int j = j0 + 64 + lane; j < j1; j += 64) m = fmaxf(m, ml_ws[first + (size_t)j * stride].x);
+  m = wave_max(m);
+  for (int base = j0; base < j1; base += 64) {
+    const float2 ml = base == j0 ? ml0
+                                 : (base + lane < j1 ? ml_ws[first + (size_t)(base + lane) * stride]
+                                                     : make_float2(-INFINITY, 0.f));
+    const float wj = base + lane < j1 ? fast_exp2(ml.x - m) : 0.f;
+    lsum += wj * ml.y;
+    const int cnt = j1 - base < 64 ? j1 - base : 64;
+    for (int s0 = 0; s0 < cnt; s0 += 2 * kMergeBatch) {
+      if (base + s0 > j0) load_parts(base + s0);
+#pragma unroll
+      for (int u = 0; u < kMergeBatch; ++u) acc += __shfl(wj, s0 + 2 * u + half) * part[u];
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], 32);
+  if constexpr (kSegWaves > 1) {
+    __shared__ __attribute__((aligned(16))) float red_o[kSegWaves][kHeadDim];
+    __shared__ float2 red_ml[kSegWaves];
+    if (half == 0) *reinterpret_cast<f32x4*>(&red_o[sw][d]) = acc;
+    if (lane == 0) red_ml[sw] = make_float2(m, lsum);
+    __syncthreads();
+    if (sw > 0) return;
+    const float2 ml = red_ml[lane & (kSegWaves - 1)];
+    const float top = wave_max(ml.x);
+    const float wt = fast_exp2(ml.x - top);  // of wave lane % kSegWaves
+    lsum = 0.f;
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kSegWaves; ++w) {
+      const float ww = __shfl(wt, w);
+      lsum += ww * red_ml[w].y;
+      acc += ww * *reinterpret_cast<const f32x4*>(&red_o[w][d]);
+    }
+  }
+  if (half == 0) store4<OutT>(orow, acc * (1.0f / lsum));
 }
 
 // ------------------------------------------------------------ host side
@@ -571,7 +619,11 @@ int resident_waves(int32_t out_dtype, int wgw, int64_t per_cu[2]) {
     hipError_t e =
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernels[layout], 64 * wgw, (size_t)wgw * kTileBytes);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-    per_cu[layout] = n < 1 ? 1 : (int64_t)n * wgw;
+    // no more than the kernel is compiled for, also where its registers would
+    // let another wave in: 12/2 heads, 40 paged sequences, 24.5 us with 12 waves
+    // per CU against 22.7 with 8 (shorter ranges, half as many partials again)
+    const int64_t most = 4 * (layout == 1 ? kPagedWavesPerEu : kWavesPerEu);
+    per_cu[layout] = n < 1 ? 1 : (int64_t)n * wgw < most ? (int64_t)n * wgw : most;
   }
   return CTX_OK;
 }
@@ -704,6 +756,29 @@ int ctx_decode_attn_create(const ctx_decode_attn_desc* desc, ctx_decode_attn** o
 
 namespace {
 
+template <typename OutT, int kSegWaves>
+void launch_merge_of(const Plan& p, const int32_t* lens, const ctx_decode_attn* h, OutT* out, hipStream_t s) {
+  constexpr int kHeads = merge_waves(kSegWaves) / kSegWaves;
+  const dim3 grid((unsigned)(((int64_t)p.num_seqs * p.hq + kHeads - 1) / kHeads));
+  hipLaunchKernelGGL((decode_merge_kernel<OutT, kSegWaves>), grid, dim3(64 * merge_waves(kSegWaves)), 0, s, lens, p,
+                     h->o_ws, h->ml_ws, out);
+}
+
+template <typename OutT>
+void launch_merge(const Plan& p, const int32_t* lens, const ctx_decode_attn* h, OutT* out, hipStream_t s) {
+  // Segments of an average sequence, of which a wave has 16 in flight.  Per
+  // call, 4 waves per head against 1: one sequence of 30,001 tokens 29.2 and
+  // 37.6 us, 8 of 4,000..12,000 49.8 and 51.8, 32 ragged ones (9 segments) 144.0
+  // and 144.5; but 64 sequences (5 segments) 111.4 and 109.6, 256 short ones 106
+  // and 93.  (16 waves per head: 28.4 for the one sequence, 11.2 against 10.0 for
+  // one of 1,000 tokens.)
+  const int segs = p.num_ranges / p.num_seqs + 1;
+  if (segs >= 8)
+    launch_merge_of<OutT, 4>(p, lens, h, out, s);
+  else
+    launch_merge_of<OutT, 1>(p, lens, h, out, s);
+}
+
 template <bool kPaged>
 int launch(ctx_decode_attn* h, const void* q, const void* k, const void* v, const int32_t* offs,
            const int32_t* lens, int32_t num_seqs, float scale, void* out, void* stream, const Paged& pg) {
@@ -725,7 +800,6 @@ int launch(ctx_decode_attn* h, const void* q, const void* k, const void* v, cons
   const int wgw = h->split_wgw;
   const size_t split_lds = (size_t)wgw * kTileBytes;
   const dim3 split_grid((unsigned)(p.num_ranges * p.hkv / wgw));
-  const dim3 merge_grid((unsigned)(((int64_t)num_seqs * p.hq + kMergeWaves - 1) / kMergeWaves));
   const uint16_t* qp = static_cast<const uint16_t*>(q);
   const uint16_t* kp = static_cast<const uint16_t*>(k);
   const uint16_t* vp = static_cast<const uint16_t*>(v);
@@ -733,14 +807,12 @@ int launch(ctx_decode_attn* h, const void* q, const void* k, const void* v, cons
     float* op = static_cast<float*>(out);
     hipLaunchKernelGGL((decode_split_kernel<float, kPaged>), split_grid, dim3(64 * wgw), split_lds, s, qp, kp, vp,
                        offs, lens, p, pg, h->o_ws, h->ml_ws, op);
-    hipLaunchKernelGGL(decode_merge_kernel<float>, merge_grid, dim3(64 * kMergeWaves), 0, s, lens, p,
-                       h->o_ws, h->ml_ws, op);
+    launch_merge<float>(p, lens, h, op, s);
   } else {
     uint16_t* op = static_cast<uint16_t*>(out);
     hipLaunchKernelGGL((decode_split_kernel<uint16_t, kPaged>), split_grid, dim3(64 * wgw), split_lds, s, qp, kp, vp,
                        offs, lens, p, pg, h->o_ws, h->ml_ws, op);
-    hipLaunchKernelGGL(decode_merge_kernel<uint16_t>, merge_grid, dim3(64 * kMergeWaves), 0, s, lens, p,
-                       h->o_ws, h->ml_ws, op);
+    launch_merge<uint16_t>(p, lens, h, op, s);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "kernel launch");

@@ -328,3 +328,35 @@ def test_non_finite_value_reaches_only_its_own_dimension(split):
     assert not np.isfinite(got[bad]).any(), "a planted non-finite value did not reach its dimension"
     assert np.isnan(got[1, 2 * g:3 * g, 37]).all()
     assert_parity(got[~bad], ref[~bad], f"elements beside the non-finite ones, split={split}")
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (16, 1), (12, 6)])
+@pytest.mark.parametrize("segments", [2, 3, 4, 5, 15, 16, 17, 31, 33, 64, 65, 127, 257, 300])
+def test_merge_segment_counts(hq, hkv, segments):
+    """A sequence cut into a given number of ranges, merged by four waves per
+    head (few sequences: many ranges each) and by one (a batch of short ones
+    around it): counts around one wave's 16 in flight and its 64 weights, and
+    counts that leave some of the four waves without a segment."""
+    rng = np.random.default_rng(segments * 31 + hq)
+    w = wl.Workload("merge", 160, 1, 1, hq, hkv, 1, "uniform", 1, 2)
+    for lens, split in (([16 * segments - 5], 16), ([0, 16 * segments - 16 + 1, 7], 16)):
+        lens = np.array(lens, np.int32)
+        lay = wl.make_layout(np.maximum(lens, 1), 1)
+        q = rand_bits(rng, (len(lens), hq, 128))
+        k, v = rand_bits(rng, (lay.num_rows, hkv, 128), 3.0), rand_bits(rng, (lay.num_rows, hkv, 128))
+        ref = oracle.decode_attn(q, k, v, lay.offsets, lens, w.scale)
+        got = run(hq, hkv, q, k, v, lay.offsets, lens, w.scale, split_tokens=split, canary=True)
+        assert_parity(got, ref, f"{segments} segments, four waves per head")
+    # one long sequence among 200 short ones: 16 * ceil(total / ranges / 16) tokens per range
+    lens = np.full(200, 3, np.int32)
+    lens[77] = 32 * segments
+    lens[5] = 0
+    lay = wl.make_layout(np.maximum(lens, 1), 1)
+    q = rand_bits(rng, (200, hq, 128))
+    k, v = rand_bits(rng, (lay.num_rows, hkv, 128), 3.0), rand_bits(rng, (lay.num_rows, hkv, 128))
+    ref = oracle.decode_attn(q, k, v, lay.offsets, lens, w.scale)
+    what = f"{32 * segments} of {lens.sum()} tokens"
+    assert_parity(run(hq, hkv, q, k, v, lay.offsets, lens, w.scale, canary=True), ref, what)
+    # bf16 rounds the same fp32 values to nearest: half an ulp is at most 2^-8 of the value
+    got = run(hq, hkv, q, k, v, lay.offsets, lens, w.scale, out_dtype=torch.bfloat16, canary=True)
+    assert (np.abs(got - ref) <= 2.0**-8 * np.abs(ref) + 2e-4).all(), what
