@@ -12,18 +12,20 @@
 // Design:
 //   * opd_weight_kernel: one workgroup per response counts its supervised
 //     tokens and writes w_j = m_j / (B (M_b + eps)).
-//   * opd_row_kernel<C>: a persistent 1024-thread workgroup per CU walks the
-//     token rows; it holds a whole row in registers (thread t owns the
-//     16-byte chunks t + 1024 k, k < C: coalesced, non-temporal loads).  It reduces the row maximum and
-//     the sum of exp over the registers (wave shuffles, then 16 partials
-//     through LDS, always in the same order), forms lp, the clipped ratio,
-//     the dual-clip loss and the per-row gradient scale g, and writes the
-//     gradient row g (onehot - softmax) from the same registers, rounded to
-//     bf16.  A row whose g is 0 (a flat clipping regime or A = 0) writes
-//     zeros without the second exp pass; a masked row is not read at all.
-//     At 128 VGPRs a CU holds one such workgroup, so the next row's loads are
-//     issued chunk by chunk as the gradient pass frees the registers: its
-//     HBM reads overlap this row's exps and gradient stores.
+//   * opd_row_kernel: persistent workgroups walk the token rows; each holds a
+//     whole row in registers (thread t owns the 16-byte chunks t + kThreads k,
+//     k < C: coalesced, non-temporal loads) and has 256, 512 or 1024 threads, the
+//     fewest that can (up to 19 chunks per thread), so that a CU works on 4, 2 or
+//     1 rows (8 short ones) at different stages.  It reduces the row maximum and
+//     the sum of exp over the registers (lane moves, then the waves' partials
+//     through LDS, always in the same order), forms lp, the clipped ratio, the
+//     dual-clip loss and the per-row gradient scale g, and writes the gradient
+//     row g (onehot - softmax) from the same registers, rounded to bf16.  A row
+//     whose g is 0 (a flat clipping regime or A = 0) writes zeros without the
+//     second exp pass; a masked row is not read at all.  The next row's loads are
+//     issued chunk by chunk as the last pass frees the registers: the gradient
+//     pass, or for the loss alone the sum pass (5,716 rows of 151,936 columns:
+//     355 us when it waited for the row's end, 288 now, 5.97 TB/s).
 //   * opd_reduce_kernel: loss = sum_j w_j l_j in double precision, one
 //     workgroup, fixed order (deterministic, no atomics).
 
@@ -44,13 +46,18 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRowThreads = 1024;
-constexpr int kRowWaves = kRowThreads / 64;
+constexpr int kMaxRowThreads = 1024;
 constexpr int kChunk = 8;  // bf16 per 16-byte chunk
 constexpr int kMaxChunksPerThread = 19;  // 76 VGPRs of row data: 128 VGPRs at 16 waves per CU
-constexpr int64_t kMaxVocab = (int64_t)kRowThreads * kChunk * kMaxChunksPerThread;  // 155,648
+constexpr int64_t kMaxVocab = (int64_t)kMaxRowThreads * kChunk * kMaxChunksPerThread;  // 155,648
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+
+// Chunks per thread up to which a CU takes 32 waves of rows instead of 16: with
+// so little work per row the reductions' latency is what more rows hide (2,000
+// columns, 18,387 rows: 59 us with 32 waves, 65 with 16; with 7 chunks, 12,944
+// columns, 90 and 87).
+constexpr int kLightChunks = 4;
 
 struct OpdParams {
   float clip_log;
@@ -69,41 +76,48 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-  return x;
+// x of the lane that a data-parallel-primitive control word names, `none` where it names none
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ float dpp_or(float none, float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none), __builtin_bit_cast(int, x),
+                                                               kCtrl, kRowMask, 0xf, false));
 }
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-  return x;
+// Reduction over the wave, in a fixed order: lane 63 ends with rows of 16 lanes
+// folded by shifts of 1, 2, 4 and 8, then row by row.  Register moves, where a
+// shuffle would go through LDS six times in a row.
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float x, float none, Op op) {
+  x = op(x, dpp_or<0x111, 0xf>(none, x));
+  x = op(x, dpp_or<0x112, 0xf>(none, x));
+  x = op(x, dpp_or<0x114, 0xf>(none, x));
+  x = op(x, dpp_or<0x118, 0xf>(none, x));
+  x = op(x, dpp_or<0x142, 0xa>(none, x));  // lane 15 of rows 0 and 2 to rows 1 and 3
+  x = op(x, dpp_or<0x143, 0xc>(none, x));  // lane 31 to rows 2 and 3
+  return x;                                // complete in lane 63
 }
 
-// Block reductions over kRowWaves partials in a fixed order.
-__device__ __forceinline__ float block_max(float x, float* red) {
-  x = wave_max(x);
-  const int wave = threadIdx.x >> 6;
+// The same over a workgroup of kThreads threads: the waves' results in wave order.
+template <int kThreads, typename Op>
+__device__ __forceinline__ float block_reduce(float x, float none, float* red, Op op) {
+  x = wave_reduce(x, none, op);
   __syncthreads();  // red is free (previous reduction read it)
-  if ((threadIdx.x & 63) == 0) red[wave] = x;
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = x;
   __syncthreads();
   float r = red[0];
 #pragma unroll
-  for (int w = 1; w < kRowWaves; ++w) r = fmaxf(r, red[w]);
+  for (int w = 1; w < kThreads / 64; ++w) r = op(r, red[w]);
   return r;
 }
 
+template <int kThreads>
+__device__ __forceinline__ float block_max(float x, float* red) {
+  return block_reduce<kThreads>(x, -INFINITY, red, [](float a, float b) { return fmaxf(a, b); });
+}
+
+template <int kThreads>
 __device__ __forceinline__ float block_sum(float x, float* red) {
-  x = wave_sum(x);
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[wave] = x;
-  __syncthreads();
-  float r = red[0];
-#pragma unroll
-  for (int w = 1; w < kRowWaves; ++w) r += red[w];
-  return r;
+  return block_reduce<kThreads>(x, 0.f, red, [](float a, float b) { return a + b; });
 }
 
 __global__ __launch_bounds__(256) void opd_weight_kernel(const uint8_t* __restrict__ mask,
@@ -173,18 +187,18 @@ __device__ __forceinline__ void opaque(u32x4 (&x)[C]) {
   for (int k = 0; k < C; ++k) asm volatile("" : "+v"(x[k]));
 }
 
-template <int C>
-__global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
+template <int C, int kThreads, bool kGrad>
+__global__ __launch_bounds__(kThreads) void opd_row_kernel(
     const uint16_t* __restrict__ logits, int64_t row_stride, int32_t vocab, int32_t num_rows,
     const int32_t* __restrict__ tokens, const float* __restrict__ old_logp,
     const float* __restrict__ teacher_logp, const uint8_t* __restrict__ mask,
     const float* __restrict__ weight, OpdParams prm, float* __restrict__ token_logp,
     float* __restrict__ token_loss, uint16_t* __restrict__ grad, int64_t grad_stride) {
-  __shared__ float red[kRowWaves];
+  __shared__ float red[kThreads / 64];
   const int tid = threadIdx.x;
   const int nchunks = (vocab + kChunk - 1) / kChunk;
   const int nwhole = vocab / kChunk;  // chunks with 8 columns below vocab
-  // C = ceil(nchunks / 1024): rounds k < C - 1 give every thread a whole
+  // C = ceil(nchunks / kThreads): rounds k < C - 1 give every thread a whole
   // chunk; only the last round tests chunks and columns against vocab
   constexpr int kwhole = C - 1;
   const uint32_t load_bytes = (uint32_t)nchunks * 16u;   // loads: every chunk (the partial one padded)
@@ -192,7 +206,8 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
   const int voff = tid * 16;
 
   // Persistent: rows blockIdx.x, + gridDim.x, ...  The row is held in x; the
-  // next row's loads are issued chunk by chunk as the gradient pass frees x.
+  // next row's loads are issued chunk by chunk as the last pass over x (the
+  // gradient's, or without one the sum's) frees it.
   u32x4 x[C];
   int j = blockIdx.x;
   if (j >= num_rows) return;
@@ -201,7 +216,7 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
     const __amdgpu_buffer_rsrc_t rr = row_rsrc(logits + (size_t)j * row_stride, load_bytes);
 #pragma unroll
     for (int k = 0; k < C; ++k)
-      x[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, voff + k * kRowThreads * 16, 0,
+      x[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, voff + k * kThreads * 16, 0,
                                                                               kNonTemporal));
   }
 #pragma nounroll
@@ -214,9 +229,20 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
     const int vo = t * 16;
     const int jn = j + (int)gridDim.x;
     const bool next_sup = jn < num_rows && mask[jn] != 0;
+    const __amdgpu_buffer_rsrc_t nr = row_rsrc(logits + (size_t)(next_sup ? jn : j) * row_stride, next_sup ? load_bytes : 0u);
+    auto refill = [&](int k) {
+      x[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(nr, vo + k * kThreads * 16, 0,
+                                                                              kNonTemporal));
+    };
     float g = 0.f, lse2 = 0.f;
     int tok = -1;
     if (sup) {
+      // the token's values, asked for before the passes that they are needed after
+      tok = tokens[j];
+      const bool tok_ok = tok >= 0 && tok < vocab;
+      const float zt = tok_ok ? __uint_as_float((uint32_t)logits[(size_t)j * row_stride + tok] << 16)
+                              : __builtin_nanf("");
+      const float old = old_logp[j], teacher = teacher_logp[j], wj = weight[j];
       float mx = -INFINITY;
 #pragma unroll
       for (int k = 0; k < C; ++k) {
@@ -224,7 +250,7 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
 #pragma unroll
           for (int i = 0; i < 4; ++i) mx = fmaxf(mx, fmaxf(lo_bf16(x[k][i]), hi_bf16(x[k][i])));
         } else {
-          const int c0 = (t + k * kRowThreads) * kChunk;
+          const int c0 = (t + k * kThreads) * kChunk;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             if (c0 + 2 * i < vocab) mx = fmaxf(mx, lo_bf16(x[k][i]));
@@ -233,9 +259,11 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
         }
         __builtin_amdgcn_sched_barrier(0);  // chunk by chunk: bounded live ranges
       }
-      const float m2 = block_max(mx, red) * kLog2e;
+      const float m2 = block_max<kThreads>(mx, red) * kLog2e;
       opaque(x);
       float s = 0.f;
+      // as below: the row has landed, the refills need not wait for each other
+      if (!kGrad) __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
 #pragma unroll
       for (int k = 0; k < C; ++k) {
         if (k < kwhole) {
@@ -244,33 +272,29 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
             s += __builtin_amdgcn_exp2f(fmaf(lo_bf16(x[k][i]), kLog2e, -m2)) +
                  __builtin_amdgcn_exp2f(fmaf(hi_bf16(x[k][i]), kLog2e, -m2));
         } else {
-          const int c0 = (t + k * kRowThreads) * kChunk;
+          const int c0 = (t + k * kThreads) * kChunk;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             if (c0 + 2 * i < vocab) s += __builtin_amdgcn_exp2f(fmaf(lo_bf16(x[k][i]), kLog2e, -m2));
             if (c0 + 2 * i + 1 < vocab) s += __builtin_amdgcn_exp2f(fmaf(hi_bf16(x[k][i]), kLog2e, -m2));
           }
         }
+        if (!kGrad) refill(k);
         __builtin_amdgcn_sched_barrier(0);
       }
-      lse2 = m2 + __log2f(block_sum(s, red));  // log2 of sum_v exp(z_v)
-      opaque(x);
+      lse2 = m2 + __log2f(block_sum<kThreads>(s, red));  // log2 of sum_v exp(z_v)
+      if (kGrad) opaque(x);
 
       // per-token scalars (every thread computes them; they are uniform)
-      tok = tokens[j];
-      const bool tok_ok = tok >= 0 && tok < vocab;
-      const float zt = tok_ok ? __uint_as_float((uint32_t)logits[(size_t)j * row_stride + tok] << 16)
-                              : __builtin_nanf("");
       const float lp = zt - lse2 * kLn2;
-      const float old = old_logp[j];
-      const float a = teacher_logp[j] - old;
+      const float a = teacher - old;
       const float r = lp - old;
       const float rc = fminf(fmaxf(r, -prm.clip_log), prm.clip_log);
       const float rho = expf(rc);
       const float drho = (r > -prm.clip_log && r < prm.clip_log) ? rho : 0.f;
       float l, dl;
       dual_clip_loss(rho, a, prm, &l, &dl);
-      g = weight[j] * dl * drho;
+      g = wj * dl * drho;
       if (t == 0) {
         if (token_logp != nullptr) token_logp[j] = lp;
         token_loss[j] = l;
@@ -280,20 +304,18 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
       token_loss[j] = 0.f;
     }
 
-    // gradient row g (onehot(tok) - exp(z - lse)); zeros when g = 0 (masked
-    // rows, flat clipping regimes); then the next row's chunk k into x[k]
-    const bool has_grad = grad != nullptr;
-    const __amdgpu_buffer_rsrc_t gr = row_rsrc(has_grad ? grad + (size_t)j * grad_stride : grad, store_bytes);
-    const __amdgpu_buffer_rsrc_t nr = row_rsrc(logits + (size_t)(next_sup ? jn : j) * row_stride, load_bytes);
-    const float ng = -g;
-    // Every load of this row has landed (the passes above read them); saying
-    // so here lets the compiler issue the chunk-by-chunk refills below without
-    // waiting on each other (on the masked-row path it could not tell).
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    if (kGrad) {
+      // gradient row g (onehot(tok) - exp(z - lse)); zeros when g = 0 (masked
+      // rows, flat clipping regimes); then the next row's chunk k into x[k]
+      const __amdgpu_buffer_rsrc_t gr = row_rsrc(grad + (size_t)j * grad_stride, store_bytes);
+      const float ng = -g;
+      // Every load of this row has landed (the passes above read them); saying
+      // so here lets the compiler issue the chunk-by-chunk refills below without
+      // waiting on each other (on the masked-row path it could not tell).
+      __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
 #pragma unroll
-    for (int k = 0; k < C; ++k) {
-      const int q = t + k * kRowThreads;
-      if (has_grad) {
+      for (int k = 0; k < C; ++k) {
+        const int q = t + k * kThreads;
         u32x4 o = {0u, 0u, 0u, 0u};
         if (g != 0.f) {
 #pragma unroll
@@ -311,20 +333,21 @@ __global__ __launch_bounds__(kRowThreads) void opd_row_kernel(
         }
         if (k < C - 1 || q < nwhole) {
           __builtin_amdgcn_raw_buffer_store_b128(
-              __builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, o), gr, vo + k * kRowThreads * 16, 0,
+              __builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, o), gr, vo + k * kThreads * 16, 0,
               kNonTemporal);
         } else if (q == nwhole && nwhole < nchunks) {  // the partial chunk: its columns below vocab
           uint16_t* gp = grad + (size_t)j * grad_stride + (size_t)nwhole * kChunk;
           for (int e = 0; e < vocab - nwhole * kChunk; ++e)
             gp[e] = (uint16_t)(e & 1 ? o[e >> 1] >> 16 : o[e >> 1] & 0xffffu);
         }
+        refill(k);
+        // keep the refill of x[k] after its last use: hoisting the loads would
+        // need a second row's worth of registers
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (next_sup)
-        x[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(nr, vo + k * kRowThreads * 16, 0,
-                                                                                kNonTemporal));
-      // keep the refill of x[k] after its last use: hoisting the loads would
-      // need a second row's worth of registers
-      __builtin_amdgcn_sched_barrier(0);
+    } else if (!sup && next_sup) {
+#pragma unroll
+      for (int k = 0; k < C; ++k) refill(k);
     }
     sup = next_sup;
   }
@@ -358,13 +381,40 @@ int fail(int code, const char* fmt, ...) {
 
 bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
 
-template <int C>
-void launch_rows(int32_t n, int grid, hipStream_t s, const uint16_t* logits, int64_t stride, int32_t vocab,
-                 const int32_t* tokens, const float* old_lp, const float* tea_lp, const uint8_t* mask,
-                 const float* weight, OpdParams prm, float* token_logp, float* token_loss, uint16_t* grad,
-                 int64_t grad_stride) {
-  hipLaunchKernelGGL(opd_row_kernel<C>, dim3((unsigned)grid), dim3(kRowThreads), 0, s, logits, stride, vocab, n,
-                     tokens, old_lp, tea_lp, mask, weight, prm, token_logp, token_loss, grad, grad_stride);
+struct RowArgs {
+  const uint16_t* logits;
+  int64_t stride;
+  int32_t vocab, n;
+  const int32_t* tokens;
+  const float *old_lp, *tea_lp;
+  const uint8_t* mask;
+  const float* weight;
+  OpdParams prm;
+  float *token_logp, *token_loss;
+  uint16_t* grad;
+  int64_t grad_stride;
+  int cus;
+  hipStream_t stream;
+};
+
+template <int C, int kThreads, bool kGrad>
+void launch_rows(const RowArgs& a) {
+  // resident workgroups
+  constexpr int kPerCu = (C <= kLightChunks ? 2048 : 1024) / kThreads;
+  const int64_t most = (int64_t)a.cus * kPerCu;
+  const unsigned grid = (unsigned)(a.n < most ? a.n : most);
+  hipLaunchKernelGGL((opd_row_kernel<C, kThreads, kGrad>), dim3(grid), dim3(kThreads), 0, a.stream, a.logits, a.stride,
+                     a.vocab, a.n, a.tokens, a.old_lp, a.tea_lp, a.mask, a.weight, a.prm, a.token_logp, a.token_loss,
+                     a.grad, a.grad_stride);
+}
+
+// The kernel with exactly ceil(chunks / kThreads) chunks per thread, kLo <= that <= kHi.
+template <int kThreads, int kLo, int kHi>
+void launch_rows_of(int per_thread, const RowArgs& a) {
+  if constexpr (kLo < kHi) {
+    if (per_thread > kLo) return launch_rows_of<kThreads, kLo + 1, kHi>(per_thread, a);
+  }
+  a.grad != nullptr ? launch_rows<kLo, kThreads, true>(a) : launch_rows<kLo, kThreads, false>(a);
 }
 
 }  // namespace
@@ -408,40 +458,26 @@ extern "C" int ctx_opd_loss_run(const void* logits, int64_t row_stride, int32_t 
   if (num_tokens > 0) {
     hipLaunchKernelGGL(opd_weight_kernel, dim3((unsigned)num_seqs), dim3(256), 0, s, mask, seq_starts, num_seqs,
                        p.eps, token_weight);
-    const int64_t per_thread = ((int64_t)vocab + kChunk * kRowThreads - 1) / (kChunk * kRowThreads);
-    // one resident workgroup per CU (about 128 VGPRs x 16 waves fill it)
     int device = 0, cus = 0;
     hipError_t e = hipGetDevice(&device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return fail(CTX_ERR_HIP, "device query: %s", hipGetErrorString(e));
-    const int grid = num_tokens < cus ? num_tokens : cus;
-    const uint16_t* lg = static_cast<const uint16_t*>(logits);
-    uint16_t* gr = static_cast<uint16_t*>(grad_logits);
-#define CTX_OPD_ROWS(C)                                                                                 \
-  launch_rows<C>(num_tokens, grid, s, lg, row_stride, vocab, tokens, old_logp, teacher_logp, mask, token_weight, \
-                 prm, token_logp, token_loss, gr, grad_row_stride)
-    switch (per_thread) {  // exactly ceil(chunks / 1024) chunks per thread
-      case 1: CTX_OPD_ROWS(1); break;
-      case 2: CTX_OPD_ROWS(2); break;
-      case 3: CTX_OPD_ROWS(3); break;
-      case 4: CTX_OPD_ROWS(4); break;
-      case 5: CTX_OPD_ROWS(5); break;
-      case 6: CTX_OPD_ROWS(6); break;
-      case 7: CTX_OPD_ROWS(7); break;
-      case 8: CTX_OPD_ROWS(8); break;
-      case 9: CTX_OPD_ROWS(9); break;
-      case 10: CTX_OPD_ROWS(10); break;
-      case 11: CTX_OPD_ROWS(11); break;
-      case 12: CTX_OPD_ROWS(12); break;
-      case 13: CTX_OPD_ROWS(13); break;
-      case 14: CTX_OPD_ROWS(14); break;
-      case 15: CTX_OPD_ROWS(15); break;
-      case 16: CTX_OPD_ROWS(16); break;
-      case 17: CTX_OPD_ROWS(17); break;
-      case 18: CTX_OPD_ROWS(18); break;
-      default: CTX_OPD_ROWS(19); break;
-    }
-#undef CTX_OPD_ROWS
+    const RowArgs a{static_cast<const uint16_t*>(logits), row_stride, vocab, num_tokens, tokens, old_logp, teacher_logp,
+                    mask, token_weight, prm, token_logp, token_loss, static_cast<uint16_t*>(grad_logits),
+                    grad_row_stride, cus, s};
+    const int chunks = (vocab + kChunk - 1) / kChunk;
+    const auto per_thread = [&](int threads) { return (chunks + threads - 1) / threads; };
+    // The fewest threads whose registers hold a row: several workgroups per CU
+    // are then in different passes over their rows, where one of 1024 threads
+    // leaves the memory idle while it reduces.  Against 1024 threads: 12,944
+    // columns 90 and 133 us, 32,000 130 and 153 (512 threads: 139), the loss alone
+    // 61 and 69; 50,257 columns with 512 threads 229 and 242.
+    if (per_thread(256) <= kMaxChunksPerThread)
+      launch_rows_of<256, 1, kMaxChunksPerThread>(per_thread(256), a);
+    else if (per_thread(512) <= kMaxChunksPerThread)
+      launch_rows_of<512, kMaxChunksPerThread / 2 + 1, kMaxChunksPerThread>(per_thread(512), a);
+    else
+      launch_rows_of<1024, kMaxChunksPerThread / 2 + 1, kMaxChunksPerThread>(per_thread(1024), a);
   }
   hipLaunchKernelGGL(opd_reduce_kernel, dim3(1), dim3(1024), 0, s, token_weight, token_loss, num_tokens, loss);
   const hipError_t e = hipGetLastError();

@@ -121,6 +121,51 @@ def test_opd_edge_batches():
         assert (got["grad_logits"][:, vocab:] == -7.0).all()
 
 
+# (9 and not 1 column: with one, the gradient is g (1 - p) with p = 1, i.e. 0 up to
+# an fp32 rounding of p, at most 2^-23 |g|, and no row scale to compare it with)
+@pytest.mark.parametrize("vocab,n", [(9, 2500), (2047, 2500), (2048, 2500), (2049, 2500), (8192, 2300), (8193, 2300),
+                                     (38911, 1100), (38912, 1100), (38913, 600), (77824, 600), (77825, 300),
+                                     (155648, 300)])
+def test_opd_workgroup_sizes_and_row_turnover(vocab, n):
+    """Both sides of the vocabularies at which the workgroup or the chunks per
+    thread change, with more rows than workgroups, so that every register is
+    refilled for a next row; runs of masked rows (NaN logits, never read) fall on
+    first, middle and last rows of a workgroup.  The loss alone gives the same
+    bits as the loss with its gradient."""
+    rng = np.random.default_rng(vocab)
+    stride = (vocab + 7) // 8 * 8
+    lens = np.array([n // 3, 0, n - n // 3])
+    starts = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    mask = (rng.random(n) > 0.3).astype(np.uint8)
+    mask[:40] = 0
+    mask[-40:] = 0
+    mask[n // 2] = 1
+    tokens = rng.integers(0, vocab, n).astype(np.int32)
+    tokens[n // 2] = vocab - 1
+    z = (2 * rng.standard_normal((n, stride), dtype=np.float32))
+    z[:, vocab:] = np.nan
+    z[mask == 0] = np.nan
+    zh = wl.f32_to_bf16_bits(z)
+    zf = wl.bf16_bits_to_f32(zh)[:, :vocab]
+    lp = np.array([zf[j, tokens[j]] - np.logaddexp.reduce(zf[j].astype(np.float64)) if mask[j] else -1.0
+                   for j in range(n)])
+    old = (lp + rng.normal(0, 0.5, n)).astype(np.float32)
+    tea = (old + rng.normal(0, 1, n)).astype(np.float32)
+    b = wl.OpdBatch(starts, tokens, mask, np.zeros(n), old, tea)
+    ref = oracle.opd_loss(zh[:, :vocab], tokens, old, tea, mask, starts)
+    zd = up_bf16(zh)
+    got = run_gpu(zd, b, vocab, grad_stride=stride)
+    check_scalars(got, ref, b, f"vocab {vocab}")
+    ok = np.nonzero(~near_kink(ref, b) | (mask == 0))[0]
+    rows = np.union1d(rng.choice(ok, min(len(ok), max(20, 2_000_000 // vocab)), replace=False), ok[[0, -1]])
+    gref = oracle.opd_grad_rows(zh[:, :vocab], tokens, mask, ref["dlp"], rows)
+    check_grad_rows(got["grad_logits"][rows, :vocab], gref, ref["dlp"][rows], f"vocab {vocab}")
+    assert (got["grad_logits"][mask == 0, :vocab] == 0).all() and (got["grad_logits"][:, vocab:] == -7.0).all()
+    alone = run_gpu(zd, b, vocab, grad=False)
+    for k in ("loss", "token_logp", "token_loss", "token_weight"):
+        assert np.array_equal(got[k], alone[k]), k
+
+
 def test_opd_loss_only_matches_and_is_deterministic():
     w = wl.OPD_WORKLOADS["opd_tiny"]
     b = wl.opd_batch(w)
