@@ -15,7 +15,7 @@
 //   * opd_row_kernel: persistent workgroups walk the token rows; each holds a
 //     whole row in registers (thread t owns the 16-byte chunks t + kThreads k,
 //     k < C: coalesced, non-temporal loads) and has 256, 512 or 1024 threads, the
-//     fewest that can (up to 19 chunks per thread), so that a CU works on 4, 2 or
+//     fewest that can (up to 19 chunks per thread; 26 of 512 threads), so that a CU works on 4, 2 or
 //     1 rows (8 short ones) at different stages.  It reduces the row maximum and
 //     the sum of exp over the registers (lane moves, then the waves' partials
 //     through LDS, always in the same order), forms lp, the clipped ratio, the
@@ -49,6 +49,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxRowThreads = 1024;
 constexpr int kChunk = 8;  // bf16 per 16-byte chunk
 constexpr int kMaxChunksPerThread = 19;  // 76 VGPRs of row data: 128 VGPRs at 16 waves per CU
+// most chunks per thread of a 512-thread workgroup: still 128 VGPRs, 16 waves per CU
+constexpr int kMaxChunks512 = 26;
 constexpr int64_t kMaxVocab = (int64_t)kMaxRowThreads * kChunk * kMaxChunksPerThread;  // 155,648
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -471,13 +473,15 @@ extern "C" int ctx_opd_loss_run(const void* logits, int64_t row_stride, int32_t 
     // are then in different passes over their rows, where one of 1024 threads
     // leaves the memory idle while it reduces.  Against 1024 threads: 12,944
     // columns 90 and 133 us, 32,000 130 and 153 (512 threads: 139), the loss alone
-    // 61 and 69; 50,257 columns with 512 threads 229 and 242.
+    // 61 and 69; 50,257 columns with 512 threads 229 and 242, 100,277 (25 chunks
+    // per thread) 466 and 476, alone 179 and 193.  With 256 threads 20 to 26
+    // chunks gain nothing: 45,000 columns 206 and (512 threads) 203.
     if (per_thread(256) <= kMaxChunksPerThread)
       launch_rows_of<256, 1, kMaxChunksPerThread>(per_thread(256), a);
-    else if (per_thread(512) <= kMaxChunksPerThread)
-      launch_rows_of<512, kMaxChunksPerThread / 2 + 1, kMaxChunksPerThread>(per_thread(512), a);
+    else if (per_thread(512) <= kMaxChunks512)
+      launch_rows_of<512, kMaxChunksPerThread / 2 + 1, kMaxChunks512>(per_thread(512), a);
     else
-      launch_rows_of<1024, kMaxChunksPerThread / 2 + 1, kMaxChunksPerThread>(per_thread(1024), a);
+      launch_rows_of<1024, kMaxChunks512 / 2 + 1, kMaxChunksPerThread>(per_thread(1024), a);
   }
   hipLaunchKernelGGL(opd_reduce_kernel, dim3(1), dim3(1024), 0, s, token_weight, token_loss, num_tokens, loss);
   const hipError_t e = hipGetLastError();

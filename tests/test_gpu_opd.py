@@ -124,7 +124,7 @@ def test_opd_edge_batches():
 # (9 and not 1 column: with one, the gradient is g (1 - p) with p = 1, i.e. 0 up to
 # an fp32 rounding of p, at most 2^-23 |g|, and no row scale to compare it with)
 @pytest.mark.parametrize("vocab,n", [(9, 2500), (2047, 2500), (2048, 2500), (2049, 2500), (8192, 2300), (8193, 2300),
-                                     (38911, 1100), (38912, 1100), (38913, 600), (77824, 600), (77825, 300),
+                                     (38911, 1100), (38912, 1100), (38913, 600), (77825, 600), (106496, 600), (106497, 300),
                                      (155648, 300)])
 def test_opd_workgroup_sizes_and_row_turnover(vocab, n):
     """Both sides of the vocabularies at which the workgroup or the chunks per
