@@ -120,7 +120,9 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // consecutive workgroups go to different XCDs; keep every tile of a unit on
   // one XCD so that its L2 serves the tiles' re-reads of the unit's K/V
   const int slot = blockIdx.x / kXcds;
-  const int tile = slot % pp.tiles;
+  // last tile first: it sees the most tokens, and started last it ran on alone
+  // (12 fresh prompts of 200..2,000 tokens 132 -> 124 us)
+  const int tile = pp.tiles - 1 - slot % pp.tiles;
   const int unit = (slot / pp.tiles) * kXcds + (int)(blockIdx.x % kXcds);
   if (unit >= pp.units) return;
   const int kv = unit % pp.hkv;
