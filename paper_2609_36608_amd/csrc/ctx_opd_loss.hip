@@ -61,6 +61,14 @@ constexpr float kLn2 = 0.6931471805599453f;
 // columns, 90 and 87).
 constexpr int kLightChunks = 4;
 
+// Calls of up to kOwnWeightTokens tokens whose rows take 256 threads find each
+// row's weight in the row kernel, which saves the launch of opd_weight_kernel (a
+// small call is bound by its launches) for at most one read of the mask, 2 KiB
+// from L2, per row.  Longer rows keep the launch: the work would take them past
+// the registers that let two workgroups share a CU.
+constexpr int32_t kOwnWeightTokens = 2048;
+constexpr int kOwnWeightThreads = 256;
+
 struct OpdParams {
   float clip_log;
   float delta;
@@ -140,6 +148,28 @@ __global__ __launch_bounds__(256) void opd_weight_kernel(const uint8_t* __restri
   for (int j = s0 + (int)threadIdx.x; j < s1; j += 256) weight[j] = mask[j] ? w : 0.f;
 }
 
+// w_j of a supervised row j, by one wave: the row's response (the first that ends
+// after it) and a count of its supervised tokens, as opd_weight_kernel has them.
+__device__ __forceinline__ float row_weight(const uint8_t* __restrict__ mask, const int32_t* __restrict__ seq_starts,
+                                            int32_t num_seqs, float eps, int j) {
+  const int lane = threadIdx.x & 63;
+  int b = 0;
+  for (int base = 0; base < num_seqs; base += 64) {
+    const unsigned long long after = __ballot(base + lane < num_seqs && seq_starts[base + lane + 1] > j);
+    if (after != 0) {
+      b = base + __builtin_ctzll(after);
+      break;
+    }
+  }
+  const int s0 = seq_starts[b], s1 = seq_starts[b + 1];
+  int mb = 0;
+  for (int base = s0; base < s1; base += 64) {
+    const int i = base + lane;
+    mb += __builtin_popcountll(__ballot(i < s1 && mask[i < s1 ? i : s0] != 0));
+  }
+  return (float)(1.0 / ((double)num_seqs * ((double)mb + (double)eps)));
+}
+
 // eq:opd-dual-clip for one token: the loss and d loss / d rho
 __device__ __forceinline__ void dual_clip_loss(float rho, float a, const OpdParams& p, float* loss,
                                                float* dloss) {
@@ -194,9 +224,12 @@ __global__ __launch_bounds__(kThreads) void opd_row_kernel(
     const uint16_t* __restrict__ logits, int64_t row_stride, int32_t vocab, int32_t num_rows,
     const int32_t* __restrict__ tokens, const float* __restrict__ old_logp,
     const float* __restrict__ teacher_logp, const uint8_t* __restrict__ mask,
-    const float* __restrict__ weight, OpdParams prm, float* __restrict__ token_logp,
-    float* __restrict__ token_loss, uint16_t* __restrict__ grad, int64_t grad_stride) {
+    float* __restrict__ weight, const int32_t* __restrict__ seq_starts, int32_t num_seqs, OpdParams prm,
+    float* __restrict__ token_logp, float* __restrict__ token_loss, uint16_t* __restrict__ grad,
+    int64_t grad_stride) {
   __shared__ float red[kThreads / 64];
+  // a row's weight computed here, or read as opd_weight_kernel has written it
+  const bool own_weights = kThreads == kOwnWeightThreads && seq_starts != nullptr;
   const int tid = threadIdx.x;
   const int nchunks = (vocab + kChunk - 1) / kChunk;
   const int nwhole = vocab / kChunk;  // chunks with 8 columns below vocab
@@ -244,7 +277,8 @@ __global__ __launch_bounds__(kThreads) void opd_row_kernel(
       const bool tok_ok = tok >= 0 && tok < vocab;
       const float zt = tok_ok ? __uint_as_float((uint32_t)logits[(size_t)j * row_stride + tok] << 16)
                               : __builtin_nanf("");
-      const float old = old_logp[j], teacher = teacher_logp[j], wj = weight[j];
+      const float old = old_logp[j], teacher = teacher_logp[j];
+      const float wj = own_weights ? row_weight(mask, seq_starts, num_seqs, prm.eps, j) : weight[j];
       float mx = -INFINITY;
 #pragma unroll
       for (int k = 0; k < C; ++k) {
@@ -300,10 +334,12 @@ __global__ __launch_bounds__(kThreads) void opd_row_kernel(
       if (t == 0) {
         if (token_logp != nullptr) token_logp[j] = lp;
         token_loss[j] = l;
+        if (own_weights) weight[j] = wj;
       }
     } else if (t == 0) {  // no loss, no gradient, logits not read
       if (token_logp != nullptr) token_logp[j] = 0.f;
       token_loss[j] = 0.f;
+      if (own_weights) weight[j] = 0.f;
     }
 
     if (kGrad) {
@@ -390,7 +426,9 @@ struct RowArgs {
   const int32_t* tokens;
   const float *old_lp, *tea_lp;
   const uint8_t* mask;
-  const float* weight;
+  float* weight;
+  const int32_t* seq_starts;  // null: the weights are there already
+  int32_t num_seqs;
   OpdParams prm;
   float *token_logp, *token_loss;
   uint16_t* grad;
@@ -406,8 +444,8 @@ void launch_rows(const RowArgs& a) {
   const int64_t most = (int64_t)a.cus * kPerCu;
   const unsigned grid = (unsigned)(a.n < most ? a.n : most);
   hipLaunchKernelGGL((opd_row_kernel<C, kThreads, kGrad>), dim3(grid), dim3(kThreads), 0, a.stream, a.logits, a.stride,
-                     a.vocab, a.n, a.tokens, a.old_lp, a.tea_lp, a.mask, a.weight, a.prm, a.token_logp, a.token_loss,
-                     a.grad, a.grad_stride);
+                     a.vocab, a.n, a.tokens, a.old_lp, a.tea_lp, a.mask, a.weight, a.seq_starts, a.num_seqs, a.prm,
+                     a.token_logp, a.token_loss, a.grad, a.grad_stride);
 }
 
 // The kernel with exactly ceil(chunks / kThreads) chunks per thread, kLo <= that <= kHi.
@@ -458,17 +496,19 @@ extern "C" int ctx_opd_loss_run(const void* logits, int64_t row_stride, int32_t 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const OpdParams prm{p.log_ratio_clip, p.clip_delta, p.dual_clip, p.eps};
   if (num_tokens > 0) {
-    hipLaunchKernelGGL(opd_weight_kernel, dim3((unsigned)num_seqs), dim3(256), 0, s, mask, seq_starts, num_seqs,
-                       p.eps, token_weight);
     int device = 0, cus = 0;
     hipError_t e = hipGetDevice(&device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return fail(CTX_ERR_HIP, "device query: %s", hipGetErrorString(e));
-    const RowArgs a{static_cast<const uint16_t*>(logits), row_stride, vocab, num_tokens, tokens, old_logp, teacher_logp,
-                    mask, token_weight, prm, token_logp, token_loss, static_cast<uint16_t*>(grad_logits),
-                    grad_row_stride, cus, s};
     const int chunks = (vocab + kChunk - 1) / kChunk;
     const auto per_thread = [&](int threads) { return (chunks + threads - 1) / threads; };
+    const bool own = num_tokens <= kOwnWeightTokens && per_thread(kOwnWeightThreads) <= kMaxChunksPerThread;
+    if (!own)
+      hipLaunchKernelGGL(opd_weight_kernel, dim3((unsigned)num_seqs), dim3(256), 0, s, mask, seq_starts, num_seqs,
+                         p.eps, token_weight);
+    const RowArgs a{static_cast<const uint16_t*>(logits), row_stride, vocab, num_tokens, tokens, old_logp, teacher_logp,
+                    mask, token_weight, own ? seq_starts : nullptr, num_seqs, prm, token_logp, token_loss,
+                    static_cast<uint16_t*>(grad_logits), grad_row_stride, cus, s};
     // The fewest threads whose registers hold a row: several workgroups per CU
     // are then in different passes over their rows, where one of 1024 threads
     // leaves the memory idle while it reduces.  Against 1024 threads: 12,944

@@ -166,6 +166,34 @@ def test_opd_workgroup_sizes_and_row_turnover(vocab, n):
         assert np.array_equal(got[k], alone[k]), k
 
 
+@pytest.mark.parametrize("n", [1, 63, 65, 2047, 2048, 2049])
+@pytest.mark.parametrize("responses", [1, 63, 64, 65, 300])
+def test_opd_weights_in_the_row_kernel_and_apart(n, responses):
+    """Token counts on both sides of the one up to which the row kernel finds
+    each row's weight itself, over response counts around its search's 64 at a
+    time: empty responses in runs, at the start and at the end, responses longer
+    than a wave, fully masked ones.  The weights are exact to fp32 rounding."""
+    rng = np.random.default_rng(n * 7 + responses)
+    cuts = np.sort(rng.integers(0, n + 1, responses - 1))
+    cuts[:responses // 3] = cuts[0] if responses > 2 and rng.random() < 0.5 else 0
+    starts = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    if responses == 65:
+        starts[40:-1] = n  # the last 25 responses are empty
+    starts = np.maximum.accumulate(starts).astype(np.int32)
+    mask = (rng.random(n) > 0.4).astype(np.uint8)
+    widest = int(np.argmax(np.diff(starts)))
+    if responses > 2:
+        mask[starts[widest]:starts[widest + 1]] = 0
+    vocab = 17
+    z = wl.f32_to_bf16_bits(rng.standard_normal((n, 24)).astype(np.float32))
+    old = (-rng.exponential(1.0, n)).astype(np.float32)
+    b = wl.OpdBatch(starts, rng.integers(0, vocab, n).astype(np.int32), mask, np.zeros(n), old,
+                    (old + rng.normal(0, 1, n)).astype(np.float32))
+    ref = oracle.opd_loss(z[:, :vocab], b.tokens, b.old_lp, b.teacher_lp, b.mask, b.seq_starts)
+    for grad in (True, False):
+        check_scalars(run_gpu(up_bf16(z), b, vocab, grad=grad), ref, b, f"{n} tokens, {responses} responses")
+
+
 def test_opd_loss_only_matches_and_is_deterministic():
     w = wl.OPD_WORKLOADS["opd_tiny"]
     b = wl.opd_batch(w)
