@@ -14,5 +14,6 @@ def __getattr__(name):
     if name in __all__:
         from . import binding
 
-        return getattr(binding, name)
+        value = globals()[name] = getattr(binding, name)  # found without this function from now on
+        return value
     raise AttributeError(name)

@@ -75,6 +75,9 @@ class OpdParams(ctypes.Structure):
         super().__init__(log_ratio_clip, clip_delta, dual_clip, eps)
 
 
+_OPD_DEFAULTS = OpdParams()
+
+
 class RolloutConfig(ctypes.Structure):
     _fields_ = [("policy", ctypes.c_int32), ("num_tasks", ctypes.c_int32), ("turns", ctypes.c_int32),
                 ("max_concurrency", ctypes.c_int32)]
@@ -169,6 +172,10 @@ def _dtype_code(dtype) -> int:
 def _check_tensors(device: int, checks) -> None:
     """Each (name, tensor, dtype): that dtype, on cuda:device, contiguous."""
     for name, t, dt in checks:
+        # one short test each where nothing is wrong (get_device() is -1 on the
+        # CPU): a call on a short batch takes less GPU time than these checks did
+        if t.dtype is dt and t.is_cuda and t.get_device() == device and t.is_contiguous():
+            continue
         if t.dtype != dt:
             raise TypeError(f"{name} must be {dt}, got {t.dtype}")
         if not t.is_cuda or t.device.index != device:
@@ -182,7 +189,9 @@ def _stream_ptr(stream, device=None) -> int:
     import torch
 
     if stream is None:
-        stream = torch.cuda.current_stream(device)
+        # the handle alone, without a Stream object around it
+        index = torch.cuda.current_device() if device is None or device.index is None else device.index
+        return torch._C._cuda_getCurrentRawStream(index)
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -361,12 +370,14 @@ def opd_loss(logits, tokens, old_logp, teacher_logp, mask, seq_starts, params: O
     import torch
 
     lib = load_library()
-    params = params or OpdParams()
+    params = params or _OPD_DEFAULTS
     n = tokens.shape[0]
     dev = logits.device
     for name, t, dt in (("logits", logits, torch.bfloat16), ("tokens", tokens, torch.int32),
                         ("old_logp", old_logp, torch.float32), ("teacher_logp", teacher_logp, torch.float32),
                         ("mask", mask, torch.uint8), ("seq_starts", seq_starts, torch.int32)):
+        if t.dtype is dt and t.is_cuda and t.device == dev:
+            continue
         if t.dtype != dt:
             raise TypeError(f"{name} must be {dt}, got {t.dtype}")
         if not t.is_cuda or t.device != dev:
@@ -385,8 +396,8 @@ def opd_loss(logits, tokens, old_logp, teacher_logp, mask, seq_starts, params: O
     def buf(name, shape, dtype):
         t = out.get(name)
         if t is None:
-            t = torch.empty(shape, dtype=dtype, device=dev)
-        elif t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or t.device != dev:
+            return torch.empty(shape, dtype=dtype, device=dev)
+        if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or t.device != dev:
             raise ValueError(f"out[{name!r}] must be a contiguous {dtype} tensor of shape {tuple(shape)}")
         return t
 
