@@ -190,6 +190,8 @@ def _stream_ptr(stream, device=None) -> int:
 
     if stream is None:
         # the handle alone, without a Stream object around it
+        if device is not None and device.type != "cuda":
+            raise ValueError(f"Expected a cuda device, but got: {device}")
         index = torch.cuda.current_device() if device is None or device.index is None else device.index
         return torch._C._cuda_getCurrentRawStream(index)
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)

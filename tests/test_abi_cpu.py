@@ -148,3 +148,15 @@ def test_mfma_probe_rejects_bad_arguments_before_the_device(lib, args, status):
     shape, wg, iters, sink = args
     assert lib.ctx_mfma_bf16(shape, wg, iters, sink, None) == status
     assert lib.ctx_decode_attn_last_error().decode()
+
+
+def test_host_tensors_are_refused_without_a_stream():
+    """The device probes look up the current stream of their tensor's device: a
+    host tensor has none, and must not reach the library as a device pointer."""
+    import torch
+
+    src, sink = torch.zeros(1024, dtype=torch.uint8), torch.zeros(64, dtype=torch.uint8)
+    for call in (lambda: bd.ctx_hbm_read(src, sink, 1), lambda: bd.ctx_hbm_copy(src, src.clone(), 1),
+                 lambda: bd.ctx_mfma_bf16(bd.CTX_MFMA_16X16X32, 1, 1, sink)):
+        with pytest.raises(ValueError, match="cuda device"):
+            call()
