@@ -219,6 +219,43 @@ __device__ __forceinline__ void opaque(u32x4 (&x)[C]) {
   for (int k = 0; k < C; ++k) asm volatile("" : "+v"(x[k]));
 }
 
+// The largest logit of the row that the workgroup holds in x.
+// The high half of a word needs no unpacking: as a float the word lies between
+// its high bf16 and the next one further from zero, so the largest word has the
+// largest high half (the loss alone over 5,716 rows of 151,936 columns 289 -> 269
+// us: this pass overlaps no loads).  Over a non-zero low half an infinity reads
+// as NaN; a row with such a word, a NaN or +inf takes a second pass over both
+// halves unpacked.
+template <int C, int kThreads>
+__device__ __forceinline__ float row_max(const u32x4 (&x)[C], int t, int vocab, float* red) {
+  float mx = -INFINITY, mw = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < C - 1; ++k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mx = fmaxf(mx, lo_bf16(x[k][i]));
+      mw = __builtin_elementwise_maximum(mw, __uint_as_float(x[k][i]));  // keeps a NaN
+    }
+    __builtin_amdgcn_sched_barrier(0);  // chunk by chunk: bounded live ranges
+  }
+  // the last round may pass the vocabulary
+  const int c0 = (t + (C - 1) * kThreads) * kChunk;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (c0 + 2 * i < vocab) mx = fmaxf(mx, lo_bf16(x[C - 1][i]));
+    if (c0 + 2 * i + 1 < vocab) mx = fmaxf(mx, hi_bf16(x[C - 1][i]));
+  }
+  const float m = block_max<kThreads>(mw == mw ? fmaxf(mx, hi_bf16(__float_as_uint(mw))) : INFINITY, red);
+  if (C == 1 || m < INFINITY) return m;
+#pragma unroll
+  for (int k = 0; k < C - 1; ++k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mx = fmaxf(mx, hi_bf16(x[k][i]));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return block_max<kThreads>(mx, red);
+}
+
 template <int C, int kThreads, bool kGrad>
 __global__ __launch_bounds__(kThreads) void opd_row_kernel(
     const uint16_t* __restrict__ logits, int64_t row_stride, int32_t vocab, int32_t num_rows,
@@ -279,23 +316,8 @@ __global__ __launch_bounds__(kThreads) void opd_row_kernel(
                               : __builtin_nanf("");
       const float old = old_logp[j], teacher = teacher_logp[j];
       const float wj = own_weights ? row_weight(mask, seq_starts, num_seqs, prm.eps, j) : weight[j];
-      float mx = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < C; ++k) {
-        if (k < kwhole) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) mx = fmaxf(mx, fmaxf(lo_bf16(x[k][i]), hi_bf16(x[k][i])));
-        } else {
-          const int c0 = (t + k * kThreads) * kChunk;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (c0 + 2 * i < vocab) mx = fmaxf(mx, lo_bf16(x[k][i]));
-            if (c0 + 2 * i + 1 < vocab) mx = fmaxf(mx, hi_bf16(x[k][i]));
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // chunk by chunk: bounded live ranges
-      }
-      const float m2 = block_max<kThreads>(mx, red) * kLog2e;
+      float m2 = row_max<C, kThreads>(x, t, vocab, red) * kLog2e;
+      asm volatile("" : "+v"(m2));  // rounded: not fused into a sum here or there, the modes agree bit for bit
       opaque(x);
       float s = 0.f;
       // as below: the row has landed, the refills need not wait for each other
@@ -322,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void opd_row_kernel(
       if (kGrad) opaque(x);
 
       // per-token scalars (every thread computes them; they are uniform)
-      const float lp = zt - lse2 * kLn2;
+      const float lp = fmaf(-lse2, kLn2, zt);
       const float a = teacher - old;
       const float r = lp - old;
       const float rc = fminf(fmaxf(r, -prm.clip_log), prm.clip_log);

@@ -194,6 +194,62 @@ def test_opd_weights_in_the_row_kernel_and_apart(n, responses):
         check_scalars(run_gpu(up_bf16(z), b, vocab, grad=grad), ref, b, f"{n} tokens, {responses} responses")
 
 
+@pytest.mark.parametrize("vocab", [40, 2049, 9001, 40001, 151936])
+def test_opd_row_maximum_over_both_halves_of_a_word(vocab):
+    """The maximum reads the high halves of words whose low halves hold anything:
+    the largest logit in either half, at either end, of equal or opposite sign to
+    its neighbour; rows without a logit above zero; -inf entries (excluded
+    columns) next to finite ones; and +inf and NaN, whose rows have no softmax:
+    their log-probability is NaN, the other rows are untouched."""
+    rng = np.random.default_rng(vocab)
+    stride = (vocab + 7) // 8 * 8
+    rows = []
+    for at in (0, 1, vocab - 2, vocab - 1, vocab // 2 & ~1, vocab // 2 | 1):
+        for sign in (1.0, -1.0):
+            z = rng.standard_normal(vocab).astype(np.float32) - 4.0
+            z[at], z[at ^ 1 if at ^ 1 < vocab else at - 1] = 9.0, 9.0 * sign - 0.0625
+            rows.append(z)
+    rows.append(-60.0 - 3 * np.abs(rng.standard_normal(vocab)).astype(np.float32))  # all far below zero
+    rows.append(np.full(vocab, -2.5, np.float32))
+    rows.append(np.where(np.arange(vocab) % 2 == 0, -0.0, -1e-3).astype(np.float32))
+    for parity in (0, 1):  # excluded columns in one half of every word
+        z = rng.standard_normal(vocab).astype(np.float32) * 2
+        z[parity::2] = -np.inf
+        rows.append(z)
+    # all columns but two excluded (with one, p = 1 and the gradient is an fp32
+    # rounding of 1 - p, at most 2^-22 |g|, with no row scale to compare it with)
+    z = np.full(vocab, -np.inf, np.float32)
+    z[vocab // 3], z[vocab // 3 + 2] = -7.0, -6.5
+    rows.append(z)
+    n_good = len(rows)
+    for value in (np.inf, np.nan):
+        for at in (4, 5):
+            z = rng.standard_normal(vocab).astype(np.float32)
+            z[at] = value
+            rows.append(z)
+    n = len(rows)
+    zf = np.zeros((n, stride), np.float32)
+    zf[:, :vocab] = np.stack(rows)
+    zh = wl.f32_to_bf16_bits(zf)
+    tokens = np.array([int(np.argmax(np.where(np.isfinite(r), r, -np.inf))) for r in rows], np.int32)
+    old = np.full(n, -0.7, np.float32)
+    tea = (old + rng.normal(0, 1, n)).astype(np.float32)
+    starts = np.array([0, n_good, n], np.int32)
+    b = wl.OpdBatch(starts, tokens, np.ones(n, np.uint8), np.zeros(n), old, tea)
+    good = wl.OpdBatch(starts[:2], tokens[:n_good], np.ones(n_good, np.uint8), np.zeros(n_good), old[:n_good],
+                       tea[:n_good])
+    ref = oracle.opd_loss(zh[:n_good, :vocab], good.tokens, good.old_lp, good.teacher_lp, good.mask, good.seq_starts)
+    got = run_gpu(up_bf16(zh[:n_good].copy()), good, vocab)
+    check_scalars(got, ref, good, f"vocab {vocab}")
+    picks = np.nonzero(~near_kink(ref, good))[0]
+    gref = oracle.opd_grad_rows(zh[:n_good, :vocab], good.tokens, good.mask, ref["dlp"], picks)
+    check_grad_rows(got["grad_logits"][picks], gref, ref["dlp"][picks], f"vocab {vocab}")
+    for grad in (True, False):
+        got = run_gpu(up_bf16(zh), b, vocab, grad=grad)
+        np.testing.assert_allclose(got["token_logp"][:n_good], ref["lp"], rtol=0, atol=LP_ATOL)
+        assert np.isnan(got["token_logp"][n_good:]).all()
+
+
 def test_opd_loss_only_matches_and_is_deterministic():
     w = wl.OPD_WORKLOADS["opd_tiny"]
     b = wl.opd_batch(w)
