@@ -62,8 +62,8 @@ typedef struct {
   int32_t num_kv_heads; /* Hkv, the shared KV heads (e.g. 8) */
   int32_t head_dim;     /* D; only 128 is supported */
   int32_t max_batch;    /* upper bound on num_seqs in any run call (sizes the workspace) */
-  int32_t max_seq_len;  /* upper bound on any seq_lens[b]; only sizes the workspace when
-                           split_tokens > 0 */
+  int32_t max_seq_len;  /* upper bound on any seq_lens[b]; sizes the workspace when
+                           split_tokens > 0, else only guides the prefill's choice of kernel */
   ctx_dtype out_dtype;  /* F32, or BF16 = round-to-nearest-even of the fp32 result */
   int32_t split_tokens; /* 0: balanced split of the batch's tokens over the GPU (default);
                            >= 16: every work range holds exactly this many tokens

@@ -61,6 +61,7 @@ struct PrefillPlan {
   int32_t group;
   int32_t tiles;  // workgroups per (sequence, KV head)
   int32_t units;  // sequences x KV heads
+  int32_t last_first;  // the tiles of a unit in falling order
   float scale_log2;
 };
 
@@ -93,7 +94,7 @@ __device__ __forceinline__ float max8(float a, float b, float c, float d, float 
   return mx(mx(mx(mx(a, b), c), mx(mx(d, e), f)), mx(g, h));
 }
 
-template <typename OutT, bool kSplitP, bool kSplitKv>
+template <typename OutT, bool kSplitP, bool kSplitKv, bool kShort>
 __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2))) void prefill_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
     const int32_t* __restrict__ offs, const int32_t* __restrict__ lens,
@@ -120,9 +121,10 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // consecutive workgroups go to different XCDs; keep every tile of a unit on
   // one XCD so that its L2 serves the tiles' re-reads of the unit's K/V
   const int slot = blockIdx.x / kXcds;
-  // last tile first: it sees the most tokens, and started last it ran on alone
-  // (12 fresh prompts of 200..2,000 tokens 132 -> 124 us)
-  const int tile = pp.tiles - 1 - slot % pp.tiles;
+  // In a grid that is not resident at once, last tile first: it sees the most
+  // tokens, and started last it ran on alone (12 fresh prompts of 200..2,000
+  // tokens 132 -> 124 us).
+  const int tile = pp.last_first ? pp.tiles - 1 - slot % pp.tiles : slot % pp.tiles;
   const int unit = (slot / pp.tiles) * kXcds + (int)(blockIdx.x % kXcds);
   if (unit >= pp.units) return;
   const int kv = unit % pp.hkv;
@@ -394,11 +396,30 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     };
     issue(0, lds_k0, lds_v0);
     issue(kPrefillBlock, lds_k1, lds_v1);
-    // block j in stage j % 3; step j issues block j + 2 into stage (j + 2) % 3
-    for (int t0 = 0; t0 < kv_end; t0 += 3 * kPrefillBlock) {
-      step(t0, lds_k0, lds_v0, lds_k2, lds_v2);
-      step(t0 + kPrefillBlock, lds_k1, lds_v1, lds_k0, lds_v0);
-      step(t0 + 2 * kPrefillBlock, lds_k2, lds_v2, lds_k1, lds_v1);
+    // Block j in stage j % 3; step j issues block j + 2 into stage (j + 2) % 3.
+    // An exit in the middle of the loop would join its head and make the compiler
+    // wait there for loads that no path to it leaves unfinished, so the loop runs
+    // whole rounds of three steps, the last of them on empty blocks.  For short
+    // contexts, where those count, the last one or two blocks come after the loop
+    // (134 fresh prompts of 37..92 tokens 65.5 -> 62.5 us; the longer code costs
+    // the burst over long histories 10.28 -> 10.60 ms).
+    if constexpr (kShort) {
+      int t0 = 0;
+      for (; t0 + 2 * kPrefillBlock < kv_end; t0 += 3 * kPrefillBlock) {
+        step(t0, lds_k0, lds_v0, lds_k2, lds_v2);
+        step(t0 + kPrefillBlock, lds_k1, lds_v1, lds_k0, lds_v0);
+        step(t0 + 2 * kPrefillBlock, lds_k2, lds_v2, lds_k1, lds_v1);
+      }
+      if (t0 < kv_end) {
+        step(t0, lds_k0, lds_v0, lds_k2, lds_v2);
+        if (t0 + kPrefillBlock < kv_end) step(t0 + kPrefillBlock, lds_k1, lds_v1, lds_k0, lds_v0);
+      }
+    } else {
+      for (int t0 = 0; t0 < kv_end; t0 += 3 * kPrefillBlock) {
+        step(t0, lds_k0, lds_v0, lds_k2, lds_v2);
+        step(t0 + kPrefillBlock, lds_k1, lds_v1, lds_k0, lds_v0);
+        step(t0 + 2 * kPrefillBlock, lds_k2, lds_v2, lds_k1, lds_v1);
+      }
     }
     // no load may land in LDS after the workgroup has released it
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
@@ -516,19 +537,21 @@ struct PrefillArgs {
   hipStream_t stream;
 };
 
-template <typename OutT, bool kSplitP, bool kSplitKv>
+template <typename OutT, bool kSplitP, bool kSplitKv, bool kShort>
 void launch_one(const PrefillArgs& a) {
-  hipLaunchKernelGGL((prefill_kernel<OutT, kSplitP, kSplitKv>), dim3(a.grid), dim3(64 * kPrefillWaves), 0,
+  hipLaunchKernelGGL((prefill_kernel<OutT, kSplitP, kSplitKv, kShort>), dim3(a.grid), dim3(64 * kPrefillWaves), 0,
                      a.stream, a.q, a.kc, a.vc, a.offs, a.lens, a.q_starts, a.q_lens, a.plan,
                      static_cast<OutT*>(a.out));
 }
 
 template <typename OutT, bool kSplitP>
-void launch_prefill(const PrefillArgs& a, bool split_kv) {
+void launch_prefill(const PrefillArgs& a, bool split_kv, bool short_kv) {
   if (split_kv)
-    launch_one<OutT, kSplitP, true>(a);
+    launch_one<OutT, kSplitP, true, false>(a);
+  else if (short_kv)
+    launch_one<OutT, kSplitP, false, true>(a);
   else
-    launch_one<OutT, kSplitP, false>(a);
+    launch_one<OutT, kSplitP, false, false>(a);
 }
 
 }  // namespace
@@ -560,14 +583,25 @@ extern "C" int ctx_prefill_attn_run(ctx_decode_attn* h, const void* q, const voi
   const int64_t cols = (int64_t)max_q_len * g;
   const int64_t units = round_up(pp.units, kXcds);  // padded to whole XCD rounds
   const int64_t whole = units * ((cols + kPrefillCols - 1) / kPrefillCols);
-  // A CU holds two workgroups of either kind.  Where the wide ones would not
-  // fill the chip even once, the narrow ones (4 times as many, each through a
-  // quarter of the tokens) do: one request with 301 new tokens over 8,000 (56
-  // wide workgroups) 219 -> 65 us, 8 requests (448, two-term weights) 255 -> 219;
-  // with more they lose, since they read every K/V block 4 times as often: 16
-  // requests (1,408) 631 against 733 us, 64 requests 2,806 against 3,244.
-  const bool split_kv = whole <= 2 * (int64_t)h->num_cus;
-  const int64_t blocks = split_kv ? units * ((cols + kSplitCols - 1) / kSplitCols) : whole;
+  // A CU holds two workgroups of either kind.  As long as the narrow ones (4
+  // times as many, each through a quarter of the tokens) are all resident at
+  // once, they finish first at any context length: one request with 301 new
+  // tokens over 8,000 (208 narrow workgroups) 65 us against 219, with 60 over 600
+  // 11.5 and 20.9.  In a second round each pays its start and its merge again,
+  // which only long contexts win back, and their length is not known here: 4
+  // requests over 4,096..12,288 tokens 237 against 342 us, but 8 fresh prompts of
+  // 300 tokens 40 against 22.5, 30 requests with 60..90 over 1,200 64 against 46.
+  // One per CU is the limit where they are no more than the wide ones (64 requests
+  // with up to 12 new tokens each 33.0 against 32.1 us), or where the handle's
+  // bound says that no wave can have three blocks (32 requests over up to 148
+  // tokens 13.5 against 12.2 us).
+  const int64_t narrow = units * ((cols + kSplitCols - 1) / kSplitCols);
+  const int per_cu = narrow == whole || d.max_seq_len <= 2 * kPrefillWaves * kPrefillBlock ? 1 : 2;
+  const bool split_kv = narrow <= per_cu * (int64_t)h->num_cus;
+  // up to 16 blocks at most: the last two steps of the wide kernel's loop count
+  const bool short_kv = d.max_seq_len <= 16 * kPrefillBlock;
+  const int64_t blocks = split_kv ? narrow : whole;
+  pp.last_first = blocks > 2 * (int64_t)h->num_cus;
   pp.tiles = (int32_t)(blocks / units);
   if (whole > INT32_MAX) return fail(CTX_ERR_INVALID_ARG, "prefill grid too large");
   const PrefillArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
@@ -575,9 +609,9 @@ extern "C" int ctx_prefill_attn_run(ctx_decode_attn* h, const void* q, const voi
                       (unsigned)blocks, reinterpret_cast<hipStream_t>(stream)};
   const bool split_p = (flags & CTX_PREFILL_SPLIT_P) != 0;
   if (d.out_dtype == CTX_DTYPE_F32)
-    split_p ? launch_prefill<float, true>(a, split_kv) : launch_prefill<float, false>(a, split_kv);
+    split_p ? launch_prefill<float, true>(a, split_kv, short_kv) : launch_prefill<float, false>(a, split_kv, short_kv);
   else
-    split_p ? launch_prefill<uint16_t, true>(a, split_kv) : launch_prefill<uint16_t, false>(a, split_kv);
+    split_p ? launch_prefill<uint16_t, true>(a, split_kv, short_kv) : launch_prefill<uint16_t, false>(a, split_kv, short_kv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return CTX_OK;

@@ -130,12 +130,13 @@ def test_prefill_last_row_equals_decode():
 
 
 @pytest.mark.parametrize("split_p", MODES)
-@pytest.mark.parametrize("hq,hkv,hist", [(32, 8, (0, 0)), (32, 8, (0, 300)), (16, 8, (120, 140)), (14, 2, (1, 400)),
+@pytest.mark.parametrize("hq,hkv,hist", [(32, 8, (0, 0)), (32, 8, (0, 300)), (16, 8, (120, 140)), (14, 2, (1, 300)),
                                          (16, 1, (31, 33))])
 def test_prefill_narrow_and_wide_workgroups(hq, hkv, hist, split_p):
     """The same queries through both kinds of workgroup: max_q_len sizes the
     grid, and a generous bound takes the call past the size up to which the
-    narrow ones (48 columns, the tokens shared out over the waves) are used.
+    narrow ones (48 columns, the tokens shared out over the waves) are used: a
+    sequence at a time against all of them at once under such a bound.
     Query counts around the edges of both tiles (48 and 192 columns), token
     counts that leave some waves of a narrow workgroup without a block, and
     unequal keys (the waves' running maxima differ)."""
@@ -153,13 +154,27 @@ def test_prefill_narrow_and_wide_workgroups(hq, hkv, hist, split_p):
     q = rand_bits(rng, (int(nq.sum()), hq, 128))
     ref = oracle.prefill_attn(q, k, v, lay.offsets, lens, qs, nq, w.scale)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    for bound in (int(nq.max()), 192 * 2 * cus + 1):  # one KV head and one sequence already exceed 2 workgroups per CU
-        with DecodeAttention(hq, hkv, len(lens), int(lens.max())) as attn:
-            out = torch.full(q.shape, -555.0, dtype=torch.float32, device=dev())
-            attn.prefill(up_bf16(q), up_bf16(k), up_bf16(v), up_i32(lay.offsets), up_i32(lens), up_i32(qs),
-                         up_i32(nq), bound, w.scale, out, split_p=split_p)
-            torch.cuda.synchronize()
-        assert_parity(out.cpu().numpy(), ref, f"{hq}/{hkv} max_q_len {bound} split_p={split_p}", tight=split_p)
+    with DecodeAttention(hq, hkv, len(lens), 4096) as attn:
+        dq, dk, dv = up_bf16(q), up_bf16(k), up_bf16(v)
+        offs, dl, dqs, dnq = up_i32(lay.offsets), up_i32(lens), up_i32(qs), up_i32(nq)
+        wide = torch.full(q.shape, -555.0, dtype=torch.float32, device=dev())
+        # one column per CU and more: even 1 KV head exceeds two narrow workgroups per CU
+        attn.prefill(dq, dk, dv, offs, dl, dqs, dnq, 48 * 2 * cus + 1, w.scale, wide, split_p=split_p)
+        narrow = torch.full(q.shape, -555.0, dtype=torch.float32, device=dev())
+        for i in range(len(lens)):
+            assert 8 * -(-hkv // 8) * -(-int(nq[i]) * g // 48) <= 2 * cus
+            one = slice(i, i + 1)
+            attn.prefill(dq, dk, dv, offs[one], dl[one], dqs[one], dnq[one], int(nq[i]), w.scale, narrow,
+                         split_p=split_p)
+        torch.cuda.synchronize()
+    # the wide kernel for handles of short contexts
+    with DecodeAttention(hq, hkv, len(lens), 512) as attn:
+        short = torch.full(q.shape, -555.0, dtype=torch.float32, device=dev())
+        attn.prefill(dq, dk, dv, offs, dl, dqs, dnq, 48 * 2 * cus + 1, w.scale, short, split_p=split_p)
+        torch.cuda.synchronize()
+    assert torch.equal(short, wide)
+    for name, out in (("wide", wide), ("narrow", narrow)):
+        assert_parity(out.cpu().numpy(), ref, f"{hq}/{hkv} {name} split_p={split_p}", tight=split_p)
 
 
 def test_prefill_abi():
