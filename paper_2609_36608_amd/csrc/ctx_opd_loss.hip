@@ -86,33 +86,32 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// x of the lane that a data-parallel-primitive control word names, `none` where it names none
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ float dpp_or(float none, float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none), __builtin_bit_cast(int, x),
-                                                               kCtrl, kRowMask, 0xf, false));
+// x of the lane kBy further round in the row of 16
+template <int kBy>
+__device__ __forceinline__ float row_rotate(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x120 + kBy, 0xf, 0xf, false));
 }
 
-// Reduction over the wave, in a fixed order: lane 63 ends with rows of 16 lanes
-// folded by shifts of 1, 2, 4 and 8, then row by row.  Register moves, where a
-// shuffle would go through LDS six times in a row.
+// Reduction over the wave, in a fixed order: halves of 32 and 16 lanes by
+// shuffles, then of 8, 4, 2 and 1 by rotations of the rows, where the lanes that
+// far apart hold the same (register moves instead of trips through LDS).  Every
+// lane ends with the result.
 template <typename Op>
-__device__ __forceinline__ float wave_reduce(float x, float none, Op op) {
-  x = op(x, dpp_or<0x111, 0xf>(none, x));
-  x = op(x, dpp_or<0x112, 0xf>(none, x));
-  x = op(x, dpp_or<0x114, 0xf>(none, x));
-  x = op(x, dpp_or<0x118, 0xf>(none, x));
-  x = op(x, dpp_or<0x142, 0xa>(none, x));  // lane 15 of rows 0 and 2 to rows 1 and 3
-  x = op(x, dpp_or<0x143, 0xc>(none, x));  // lane 31 to rows 2 and 3
-  return x;                                // complete in lane 63
+__device__ __forceinline__ float wave_reduce(float x, Op op) {
+  x = op(x, __shfl_xor(x, 32));
+  x = op(x, __shfl_xor(x, 16));
+  x = op(x, row_rotate<8>(x));
+  x = op(x, row_rotate<4>(x));
+  x = op(x, row_rotate<2>(x));
+  return op(x, row_rotate<1>(x));
 }
 
 // The same over a workgroup of kThreads threads: the waves' results in wave order.
 template <int kThreads, typename Op>
-__device__ __forceinline__ float block_reduce(float x, float none, float* red, Op op) {
-  x = wave_reduce(x, none, op);
+__device__ __forceinline__ float block_reduce(float x, float* red, Op op) {
+  x = wave_reduce(x, op);
   __syncthreads();  // red is free (previous reduction read it)
-  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = x;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
   float r = red[0];
 #pragma unroll
@@ -122,12 +121,12 @@ __device__ __forceinline__ float block_reduce(float x, float none, float* red, O
 
 template <int kThreads>
 __device__ __forceinline__ float block_max(float x, float* red) {
-  return block_reduce<kThreads>(x, -INFINITY, red, [](float a, float b) { return fmaxf(a, b); });
+  return block_reduce<kThreads>(x, red, [](float a, float b) { return fmaxf(a, b); });
 }
 
 template <int kThreads>
 __device__ __forceinline__ float block_sum(float x, float* red) {
-  return block_reduce<kThreads>(x, 0.f, red, [](float a, float b) { return a + b; });
+  return block_reduce<kThreads>(x, red, [](float a, float b) { return a + b; });
 }
 
 __global__ __launch_bounds__(256) void opd_weight_kernel(const uint8_t* __restrict__ mask,
