@@ -284,6 +284,12 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     if (__any(over > 0.f)) {
 #pragma unroll
       for (int ct = 0; ct < kTiles; ++ct) {
+        // A tile whose own logits stay below its thresholds keeps its maxima: a
+        // row's weights are rounded as they would be without the other tiles' rows
+        // (and rescaling all three took 65.0 us against 62.6 for the one request,
+        // 10.09 ms against 10.03 for the burst).
+        const float t1 = thr[ct], t2 = thr_raw[ct];
+        if (!__any(lm[ct] > (masked ? t1 : t2))) continue;
         const float lmax = lm[ct] * factor;
         float mx = fmaxf(lmax, __shfl_xor(lmax, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));

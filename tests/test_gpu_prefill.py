@@ -177,6 +177,41 @@ def test_prefill_narrow_and_wide_workgroups(hq, hkv, hist, split_p):
         assert_parity(out.cpu().numpy(), ref, f"{hq}/{hkv} {name} split_p={split_p}", tight=split_p)
 
 
+def wide_bound():
+    """A max_q_len that takes any call past the size up to which the narrow
+    workgroups are used (more than two of them per CU even for 1 KV head)."""
+    return 48 * 2 * torch.cuda.get_device_properties(0).multi_processor_count + 1
+
+
+@pytest.mark.parametrize("split_p", MODES)
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (14, 2), (16, 1)])
+def test_prefill_rows_do_not_depend_on_the_queries_of_other_tiles(hq, hkv, split_p):
+    """A row's running maximum, to which its softmax weights are rounded, moves
+    with the logits of its own 16 columns only: with other queries in the first
+    tile (six times as large, so that it rescales again and again), the rows of
+    every other tile keep their bits, in both kinds of workgroup."""
+    g = hq // hkv
+    nq = 192 // g + 3  # the columns of a wide workgroup and some
+    w, lay, lens, _, _, _, k, v = prefill_case(3 + hq, hq, hkv, batch=1, hist=(900, 900), new=(nq, nq))
+    rng = np.random.default_rng(hq)
+    q = rand_bits(rng, (nq, hq, 128))
+    first = (np.arange(nq)[:, None] * g + np.arange(hq) % g) < 16  # (position, head) pairs of the first tile
+    q2 = q.copy()
+    q2[first] = bf(6 * rng.standard_normal((int(first.sum()), 128)).astype(np.float32))
+    zero, n = up_i32(np.zeros(1, np.int32)), up_i32(np.array([nq], np.int32))
+    with DecodeAttention(hq, hkv, 1, 4096) as attn:
+        dk, dv, offs, dl = up_bf16(k), up_bf16(v), up_i32(lay.offsets), up_i32(lens)
+        for kind, bound in (("narrow", nq), ("wide", wide_bound())):
+            outs = []
+            for x in (q, q2):
+                out = torch.empty(q.shape, dtype=torch.float32, device=dev())
+                attn.prefill(up_bf16(x), dk, dv, offs, dl, zero, n, bound, w.scale, out, split_p=split_p)
+                torch.cuda.synchronize()
+                outs.append(out.cpu().numpy())
+            assert not np.array_equal(outs[0][first], outs[1][first])
+            assert np.array_equal(outs[0][~first], outs[1][~first]), f"{kind}: a row depends on another tile's queries"
+
+
 def test_prefill_abi():
     lib = bd.load_library()
     with DecodeAttention(32, 8, 2, 32) as attn:
