@@ -16,8 +16,8 @@
 //     with wide ones: all its waves cover the same kSplitCols = 48 columns, each
 //     for a quarter of the blocks through tiles of its own, and their partial
 //     results are merged through LDS in a fixed order.  No workspace, no second
-//     launch.  One request with 301 new tokens over 8,000: 247 us (56 wide
-//     workgroups on 256 CUs, one wave per SIMD) against 65 us.
+//     launch.  One request with 301 new tokens over 8,000: 212 us (56 wide
+//     workgroups on 256 CUs, one wave per SIMD) against 81 us.
 // Per 32 tokens and 16 columns a wave computes
 //   S^T = K Q^T                 (8 MFMA 16x16x32, K rows straight from LDS)
 //   causal mask, lazy online softmax
@@ -32,7 +32,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <cfloat>
 #include <cmath>
 #include <cstdint>
 
@@ -195,10 +194,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   for (int ct = 0; ct < kTiles; ++ct) {
     thr[ct] = -INFINITY;
     thr_raw[ct] = -INFINITY;
-    // A wave that sees only part of the tokens may meet blocks of which a column
-    // sees nothing before any that it does: the lowest finite maximum keeps
-    // 2^(-inf - m) at 0 there (the thresholds still make the first logit count).
-    st[ct] = Softmax{kSplitKv ? -FLT_MAX : -INFINITY, 0.f};
+    st[ct] = Softmax{-INFINITY, 0.f};
 #pragma unroll
     for (int nb = 0; nb < 8; ++nb) o[ct][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -248,13 +244,19 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
           sc[ct][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), qb[ct][kk], sc[ct][h], 0, 0, 0);
     }
   };
-  // the online softmax of the block at t0: its logits to weights (one or two bf16 terms)
-  auto weights = [&](int t0, f32x4 (&sc)[kTiles][2], u32x4 (&phi)[kTiles], u32x4 (&plo)[kTiles])
-      __attribute__((always_inline)) {
-    // Blocks on the causal diagonal (or past kv_end) are scaled and masked
-    // first; their logits then count as they are (factor 1, threshold thr),
-    // those of the other blocks with the factor cs (threshold thr_raw).
-    const bool masked = t0 + kPrefillBlock - 1 > mask_from;
+  // Blocks on the causal diagonal (or past kv_end) are scaled and masked first;
+  // their logits then count as they are (factor 1, threshold thr), those of the
+  // other blocks with the factor cs (threshold thr_raw).
+  auto is_masked = [&](int t0) { return t0 + kPrefillBlock - 1 > mask_from; };
+  // The block's logits ready for the softmax, and each lane's largest ones; true
+  // if some logit of the wave exceeds its running maximum by 2^8.  One test for
+  // all tiles: with a branch per tile, and the masked logits in an array of their
+  // own, the compiler moved that array through registers in every block (burst
+  // prefill 10.76 -> 10.28 ms, one wave per SIMD 247 -> 219 us).  The thresholds
+  // are read before the choice between them, a choice between the arrays would put
+  // them in memory.
+  auto maxima = [&](int t0, f32x4 (&sc)[kTiles][2], float (&lm)[kTiles]) __attribute__((always_inline)) {
+    const bool masked = is_masked(t0);
     if (masked) {
 #pragma unroll
       for (int ct = 0; ct < kTiles; ++ct)
@@ -264,15 +266,6 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
           for (int i = 0; i < 4; ++i)
             sc[ct][h][i] = (t0 + 16 * h + 4 * c + i > last_pos[ct]) ? -INFINITY : sc[ct][h][i] * cs;
     }
-    const float factor = masked ? 1.f : cs;
-    // Lazy rescale: only when some logit exceeds its running max by 2^8; the
-    // column maxima (across the 4 lanes of a column) are taken only then.  One
-    // test and one branch for all tiles: with a branch per tile, and the masked
-    // logits in an array of their own, the compiler moved that array through
-    // registers in every block (burst prefill 10.76 -> 10.28 ms, one wave per SIMD
-    // 247 -> 219 us).  The thresholds are read before the choice between them, a
-    // choice between the arrays would put them in memory.
-    float lm[kTiles];
     float over = -INFINITY;
 #pragma unroll
     for (int ct = 0; ct < kTiles; ++ct) {
@@ -281,28 +274,33 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       const float t1 = thr[ct], t2 = thr_raw[ct];
       over = fmaxf(over, lm[ct] - (masked ? t1 : t2));
     }
-    if (__any(over > 0.f)) {
+    return __any(over > 0.f);
+  };
+  // the largest of a column, whose tokens are spread over the 4 rows of 16 lanes
+  // (swaps of rows and halves between two copies: register moves, no trip through LDS)
+  auto column_max = [&](float x) {
+    const uint32_t a = __float_as_uint(x);
+    const auto rows = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const uint32_t b = __float_as_uint(fmaxf(__uint_as_float(rows[0]), __uint_as_float(rows[1])));
+    const auto halves = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+  };
+  // tile ct's running maximum becomes m; fresh: nothing has been summed yet
+  auto rescale = [&](int ct, float m, bool fresh) __attribute__((always_inline)) {
+    if (!fresh) {
+      const float alpha = fast_exp2(st[ct].m - m);
+      st[ct].l *= alpha;
 #pragma unroll
-      for (int ct = 0; ct < kTiles; ++ct) {
-        // A tile whose own logits stay below its thresholds keeps its maxima: a
-        // row's weights are rounded as they would be without the other tiles' rows
-        // (and rescaling all three took 65.0 us against 62.6 for the one request,
-        // 10.09 ms against 10.03 for the burst).
-        const float t1 = thr[ct], t2 = thr_raw[ct];
-        if (!__any(lm[ct] > (masked ? t1 : t2))) continue;
-        const float lmax = lm[ct] * factor;
-        float mx = fmaxf(lmax, __shfl_xor(lmax, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(st[ct].m, mx);
-        const float alpha = fast_exp2(st[ct].m - m_new);
-        st[ct].l *= alpha;
-#pragma unroll
-        for (int nb = 0; nb < 8; ++nb) o[ct][nb] *= alpha;
-        st[ct].m = m_new;
-        thr[ct] = m_new + kLazyRescale;
-        thr_raw[ct] = thr[ct] / cs;
-      }
+      for (int nb = 0; nb < 8; ++nb) o[ct][nb] *= alpha;
     }
+    st[ct].m = m;
+    thr[ct] = m + kLazyRescale;
+    thr_raw[ct] = thr[ct] / cs;
+  };
+  // the block's softmax weights (one or two bf16 terms)
+  auto weights = [&](int t0, const f32x4 (&sc)[kTiles][2], u32x4 (&phi)[kTiles], u32x4 (&plo)[kTiles])
+      __attribute__((always_inline)) {
+    const float factor = is_masked(t0) ? 1.f : cs;
 #pragma unroll
     for (int ct = 0; ct < kTiles; ++ct) {
       float pr[8];
@@ -395,7 +393,21 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       if (wave_active && t0 < wave_end) {
         f32x4 sc[kTiles][2];
         u32x4 phi[kTiles], plo[kTiles];
+        float lm[kTiles];
         scores(kt, sc);
+        // lazy rescale: the column maxima are taken only then
+        if (maxima(t0, sc, lm)) {
+          const bool masked = is_masked(t0);
+#pragma unroll
+          for (int ct = 0; ct < kTiles; ++ct) {
+            // A tile whose own logits stay below its thresholds keeps its maxima: a
+            // row's weights are rounded as they would be without the other tiles'
+            // rows (and rescaling all three took 10.09 ms against 10.03 for the burst).
+            const float t1 = thr[ct], t2 = thr_raw[ct];
+            if (!__any(lm[ct] > (masked ? t1 : t2))) continue;
+            rescale(ct, fmaxf(st[ct].m, column_max(lm[ct] * (masked ? 1.f : cs))), false);
+          }
+        }
         weights(t0, sc, phi, plo);
         values(vt, phi, plo);
       }
@@ -443,10 +455,25 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
   } else {
     // Wave w takes blocks w, w + 4, w + 8, ... of the workgroup's token range
-    // through its own K and V tiles, with no barrier.  A tile is refilled with
-    // the wave's next block as soon as it has been read: K while the softmax and
-    // P.V run, V while the next block's K Q^T and softmax do.
+    // through its own K and V tiles.  A tile is refilled with the wave's next
+    // block as soon as it has been read: K while the softmax and P.V run, V while
+    // the next block's K Q^T and softmax do.
+    // Every wave weighs a block against the running maximum that a pass over all
+    // blocks in order would have there, so the rounded weights are those of a wide
+    // workgroup and a row differs between the two kinds only by the order of its
+    // fp32 sums.  The maxima move rarely: of every block its wave publishes which
+    // tiles have a logit past their thresholds, and the column maxima of those, and
+    // a wave reads what the three blocks before its own have published.  The waves
+    // need not be in step for that.  301 new tokens over 8,000 with keys of equal
+    // size: 67 us, 82 with a barrier per round; 59 where each wave had maxima of its
+    // own, and weights rounded differently from a wide workgroup's.
     constexpr int kStride = kPrefillWaves * kPrefillBlock;
+    // Of block j in slot j mod kSlots: (j + 1) << kTiles | bits of the tiles.  A wave
+    // overwrites a slot four of its blocks later, when it has read of every other
+    // wave a block that follows, in that wave's order, its last look at the slot.
+    constexpr int kSlots = 4 * kPrefillWaves;
+    __shared__ uint32_t lds_over[kSlots];
+    __shared__ float lds_max[kSlots][kCols];
     uint16_t* const kt = lds_k0 + wave * kBlockElems;
     uint16_t* const vt = lds_v0 + wave * kBlockElems;
     auto issue = [&](const uint16_t* seq, int tb, uint16_t* dst) {
@@ -454,19 +481,88 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 #pragma unroll
       for (int r = 0; r < kLoads; ++r) load16_to_lds(rs, lds_row(dst, r), dvo[r]);
     };
+    // What the blocks before blk have published, one per lane, 0 past them.  Plain
+    // accesses between compiler fences: before an atomic one the compiler waits for
+    // all loads into LDS, the tiles' among them.
+    constexpr int kAhead = kPrefillWaves - 1;
+    auto published = [&](int blk) {
+      asm volatile("" ::: "memory");
+      const uint32_t word = lds_over[(blk - kAhead + lane) & (kSlots - 1)];
+      asm volatile("" ::: "memory");
+      return lane < kAhead ? word : 0u;
+    };
+    // Running maxima past the kPrefillWaves blocks from `first` of which `seen`, lane i
+    // for block first + i, has the bits of tiles with a logit past older
+    // thresholds.  Those only rise, so that no other block moves anything.
+    auto advance = [&](int first, uint32_t seen, bool fresh) __attribute__((always_inline)) {
+      // row c of 16 lanes holds block first + c, so that one test finds the next that moves
+      const bool row_masked = is_masked((first + c) * kPrefillBlock);
+      float row_max[kTiles];
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct) row_max[ct] = lds_max[(first + c) & (kSlots - 1)][ct * 16 + n];
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct) {
+        uint32_t over = (uint32_t)__ballot(seen >> ct & 1);
+        if (over == 0) continue;
+        float m = st[ct].m, t1 = thr[ct], t2 = thr_raw[ct];
+        bool moved = false;
+#pragma nounroll
+        while (true) {
+          const unsigned long long past = __ballot((over >> c & 1) && row_max[ct] > (row_masked ? t1 : t2));
+          if (past == 0) break;
+          const int i = __builtin_ctzll(past) >> 4;
+          const float mx = column_max(c == i ? row_max[ct] : -INFINITY);  // row i's to every row
+          m = fmaxf(m, is_masked((first + i) * kPrefillBlock) ? mx : mx * cs);
+          t1 = m + kLazyRescale;
+          t2 = t1 / cs;
+          moved = true;
+          over &= ~((2u << i) - 1);
+        }
+        if (moved) rescale(ct, m, fresh);
+      }
+    };
+    if (tid < kSlots) lds_over[tid] = 0;
     issue(kseq, wave * kPrefillBlock, kt);
     issue(vseq, wave * kPrefillBlock, vt);
-    // every query of the workgroup is a column of every wave, so no block below
-    // kv_end is without work
-    for (int t0 = wave * kPrefillBlock; t0 < kv_end; t0 += kStride) {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the words are zero; the loads stay in flight
+    // Every query of the workgroup is a column of every wave, so no block below
+    // kv_end is without work; one past it, in the last round, is masked for all.
+    int blk = wave;
+    for (int r0 = 0; r0 < kv_end; r0 += kStride, blk += kPrefillWaves) {
+      const int t0 = blk * kPrefillBlock;
       f32x4 sc[kTiles][2];
       u32x4 phi[kTiles], plo[kTiles];
+      float lm[kTiles];
       __builtin_amdgcn_s_waitcnt(wait_vmcnt(kLoads));  // this block's K; its V is still on the way
       asm volatile("" ::: "memory");
       scores(kt, sc);
       // the tile's reads have returned before its refill is issued
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       issue(kseq, t0 + kStride, kt);
+      uint32_t seen = published(blk);  // on its way during the test
+      uint32_t mine = 0;
+      if (maxima(t0, sc, lm)) {
+        const bool masked = is_masked(t0);
+#pragma unroll
+        for (int ct = 0; ct < kTiles; ++ct) {
+          const float t1 = thr[ct], t2 = thr_raw[ct];
+          if (!__any(lm[ct] > (masked ? t1 : t2))) continue;
+          mine |= 1u << ct;
+          const float mx = column_max(lm[ct]);
+          if (c == 0) lds_max[blk & (kSlots - 1)][ct * 16 + n] = mx;
+        }
+      }
+      // the wave's LDS accesses execute in order: who sees the word sees the maxima
+      asm volatile("" ::: "memory");
+      lds_over[blk & (kSlots - 1)] = (uint32_t)(blk + 1) << kTiles | mine;
+      asm volatile("" ::: "memory");
+      // Every wave publishes its blocks in order and waits only for earlier ones,
+      // and all are resident: the wave with the earliest block goes on.
+      const uint32_t want = lane < kAhead && blk - kAhead + lane >= 0 ? blk - kAhead + lane + 1 : 0;
+      if (mine != 0 || !__all(seen == want << kTiles)) {
+        while (!__all(seen >> kTiles == want)) seen = published(blk);
+        if (mine != 0 || !__all(seen == want << kTiles)) advance(blk - kAhead, lane == kAhead ? mine : seen, r0 == 0);
+      }
       weights(t0, sc, phi, plo);
       __builtin_amdgcn_s_waitcnt(wait_vmcnt(kLoads));  // this block's V
       asm volatile("" ::: "memory");
@@ -475,16 +571,24 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       issue(vseq, t0 + kStride, vt);
     }
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
-    __syncthreads();  // the tiles now take the waves' partial results
+    __syncthreads();
+    // past the blocks of the last round that follow this wave's
+    {
+      const int first = blk - kPrefillWaves + 1;
+      const uint32_t seen = lane < kAhead - wave ? lds_over[(first + lane) & (kSlots - 1)] : 0u;
+      if (__any(seen & ((1u << kTiles) - 1))) advance(first, seen, false);
+    }
+    // the tiles now take the waves' partial results
 
-    // Merge of the waves' partial results, one half of the dimensions at a time:
-    // wave w puts its columns' (max, sum) pairs and unnormalised outputs into its
-    // part of the tiles, 16-byte chunk ch of column j at slot ch ^ (j & 15)
-    // (conflict-free writes), and every thread adds up 4 dimensions of some columns.
+    // Merge of the waves' partial results, all relative to the same maxima, one
+    // half of the dimensions at a time: wave w puts its columns' sums and
+    // unnormalised outputs into its part of the tiles, 16-byte chunk ch of column j
+    // at slot ch ^ (j & 15) (conflict-free writes), and every thread adds up 4
+    // dimensions of some columns.
     constexpr int kHalf = kHeadDim / 2;
     constexpr int kChunks = kHalf / 4;
-    constexpr int kPartFloats = kCols * kHalf;  // then the (max, sum) pairs
-    static_assert(kPartFloats * 4 + kCols * (int)sizeof(float2) <= 2 * kBlockElems * 2,
+    constexpr int kPartFloats = kCols * kHalf;  // then the sums
+    static_assert((kPartFloats + kCols) * 4 <= 2 * kBlockElems * 2,
                   "a wave's partial results must fit half of a tile array");
     auto part_of = [&](int w) {
       return reinterpret_cast<float*>((w < 2 ? lds_k0 : lds_v0) + (w & 1) * 2 * kBlockElems);
@@ -494,7 +598,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     for (int ct = 0; ct < kTiles; ++ct) {
       float l_tot = st[ct].l + __shfl_xor(st[ct].l, 16);
       l_tot += __shfl_xor(l_tot, 32);
-      if (c == 0) reinterpret_cast<float2*>(mine + kPartFloats)[ct * 16 + n] = make_float2(st[ct].m, l_tot);
+      if (c == 0) mine[kPartFloats + ct * 16 + n] = l_tot;
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -511,20 +615,12 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
         const int col = tile * kCols + j;
         const int q_idx = col / g;
         if (q_idx >= nq) continue;
-        float2 ml[kPrefillWaves];
-        float m = -FLT_MAX;
-#pragma unroll
-        for (int w = 0; w < kPrefillWaves; ++w) {
-          ml[w] = reinterpret_cast<const float2*>(part_of(w) + kPartFloats)[j];
-          m = fmaxf(m, ml[w].x);
-        }
         float l = 0.f;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < kPrefillWaves; ++w) {
-          const float wt = fast_exp2(ml[w].x - m);
-          l += wt * ml[w].y;
-          acc += wt * *reinterpret_cast<const f32x4*>(part_of(w) + j * kHalf + ((ch ^ (j & 15)) << 2));
+          l += part_of(w)[kPartFloats + j];
+          acc += *reinterpret_cast<const f32x4*>(part_of(w) + j * kHalf + ((ch ^ (j & 15)) << 2));
         }
         const float inv = 1.0f / l;
         OutT* orow = out + ((size_t)(q_starts[b] + q_idx) * pp.hq + (size_t)kv * g + (col - q_idx * g)) * kHeadDim;

@@ -355,3 +355,167 @@ def test_prefill_bf16_weights_worst_case_against_the_rounding_bound(hq):
           f"largest err / bound {float((err / bound).max()):.3f}, largest bound {float(bound.max()):.3e}", flush=True)
     assert (err <= bound).all(), f"error above the bf16-weight rounding bound at {np.argwhere(err > bound)[:5]}"
     assert_parity(got, ref, f"prefill worst case, group {g}", tight=False)
+
+
+def through_each_kind(w, lay, lens, nq, qs, q, k, v, out_dtype=torch.float32, split_p=False):
+    """The same queries through every form of the kernel, by name: the wide
+    workgroups (a generous max_q_len), the wide ones for handles of short contexts
+    (where the contexts allow such a handle: the same loop with another end), and
+    the narrow ones (a sequence at a time)."""
+    hq, hkv = w.num_q_heads, w.num_kv_heads
+    g = hq // hkv
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    dq, dk, dv = up_bf16(q), up_bf16(k), up_bf16(v)
+    offs, dl, dqs, dnq = up_i32(lay.offsets), up_i32(lens), up_i32(qs), up_i32(nq)
+    outs = {}
+    for name, max_len in (("wide", 16384), ("wide short", 512), ("narrow", 16384)):
+        if lens.max() > max_len:
+            continue
+        out = torch.full(q.shape, -555.0, dtype=out_dtype, device=dev())
+        with DecodeAttention(hq, hkv, len(lens), max_len, out_dtype=out_dtype) as attn:
+            if name != "narrow":
+                attn.prefill(dq, dk, dv, offs, dl, dqs, dnq, wide_bound(), w.scale, out, split_p=split_p)
+            else:
+                for i in range(len(lens)):
+                    assert 8 * -(-hkv // 8) * -(-int(nq[i]) * g // 48) <= 2 * cus
+                    one = slice(i, i + 1)
+                    attn.prefill(dq, dk, dv, offs[one], dl[one], dqs[one], dnq[one], int(nq[i]), w.scale, out,
+                                 split_p=split_p)
+            torch.cuda.synchronize()
+        outs[name] = out.float().cpu().numpy()
+    return outs
+
+
+def edge_case(seed, hists, news, peaky=False):
+    """Sequences of 32/8 heads with these histories and new tokens, packed query rows."""
+    rng = np.random.default_rng(seed)
+    nq = np.array(news, np.int32)
+    lens = (np.array(hists) + nq).astype(np.int32)
+    lay = wl.make_layout(lens, 1, gap_max=5, shuffle=True, rng=rng)
+    w = wl.Workload(f"pfedge{seed}", 150 + seed % 40, 1, len(lens), 32, 8, 1, "uniform", 1, 2,
+                    peaky_frac=0.05 if peaky else 0.0)
+    k, v = wl.layer_kv_bits(w, lay, 0, fill=wl.BF16_NAN)
+    qs = np.concatenate([[0], np.cumsum(nq)[:-1]]).astype(np.int32)
+    return w, lay, lens, nq, qs, rand_bits(rng, (int(nq.sum()), 32, 128)), k, v
+
+
+# context ends around the 32-token blocks, around the rounds of four that the waves of a
+# narrow workgroup share and around the three steps of the wide loop
+ENDS = (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 255, 256, 257, 289, 384, 385)
+
+
+@pytest.mark.parametrize("split_p", MODES)
+def test_prefill_context_ends_in_each_kind(split_p):
+    """Context ends at every edge, as fresh prompts and as a few tokens over a
+    history, through each kind of workgroup: against the oracle, and the bf16
+    output of each against its own rounded fp32 output."""
+    few = [min(e, 5) for e in ENDS]
+    case = edge_case(78, [0] * len(ENDS) + [e - m for e, m in zip(ENDS, few)], list(ENDS) + few)
+    w, lay, lens, nq, qs, q, k, v = case
+    ref = oracle.prefill_attn(q, k, v, lay.offsets, lens, qs, nq, w.scale)
+    f32 = through_each_kind(*case, split_p=split_p)
+    b16 = through_each_kind(*case, out_dtype=torch.bfloat16, split_p=split_p)
+    assert list(f32) == ["wide", "wide short", "narrow"]
+    for name, out in f32.items():
+        assert_parity(out, ref, f"{name} split_p={split_p}", tight=split_p)
+        np.testing.assert_array_equal(b16[name], wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(out)), err_msg=name)
+
+
+@pytest.mark.parametrize("split_p", MODES)
+def test_prefill_constant_and_non_finite_v_in_each_kind(split_p):
+    """Equal V rows come out as that row to fp32 rounding in each kind (the bounds
+    of test_prefill_constant_v), and an infinity or a NaN in one dimension of a row
+    that every query sees stays in that dimension."""
+    case = edge_case(79, [0, 90, 100, 700, 333], [1, 20, 64, 150, 260], peaky=True)
+    w, lay, lens, nq, qs, q, k, v = case
+    row = wl.f32_to_bf16_bits(np.random.default_rng(5).standard_normal((8, 128)).astype(np.float32) * 3)
+    v = v.copy()
+    for b in range(len(lens)):
+        v[lay.offsets[b]:lay.offsets[b] + lens[b]] = row[None]
+    want = np.repeat(wl.bf16_bits_to_f32(row), 4, axis=0)[None]
+    tol = (2.0**-14 if split_p else 2.0**-16) * float(np.abs(want).max())
+    for name, out in through_each_kind(w, lay, lens, nq, qs, q, k, v, split_p=split_p).items():
+        assert np.abs(out - want).max() <= tol, name
+    for b in range(len(lens)):
+        v[lay.offsets[b], 2, 17] = 0x7F80  # +inf in token 0, KV head 2
+        v[lay.offsets[b], 5, 40] = wl.BF16_NAN
+    bad = np.zeros((32, 128), bool)
+    bad[8:12, 17] = bad[20:24, 40] = True
+    for name, out in through_each_kind(w, lay, lens, nq, qs, q, k, v, split_p=split_p).items():
+        assert not np.isfinite(out[:, bad]).any(), name
+        assert np.abs(out - want)[:, ~bad].max() <= tol, name
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (14, 2), (16, 1)])
+def test_prefill_kinds_round_the_weights_alike(hq, hkv):
+    """A row's bf16 softmax weights are the same in both kinds of workgroup: each
+    block's are rounded relative to the running maximum over the blocks up to it,
+    also where other waves had those.  Peaky keys, and keys along a component that
+    all queries share with rising logits, one in each wave's blocks, so that the
+    maxima move on the way.  Both sides sum the same products: each of
+    B blocks adds 32 of them, with at most 32 roundings, to an output element and to
+    its weights' sum, so that an element differs by at most 2 * 2 * 32 B 2^-24 times
+    the largest |V| (weights rounded to other maxima: up to 2^-8 of it)."""
+    g = hq // hkv
+    rng = np.random.default_rng(60 + hq)
+    nq = np.array([1, 40, 192 // g + 3, 100, 192 // g + 1], np.int32)
+    lens = (np.array([255, 60, 700, 900, 1000]) + nq).astype(np.int32)
+    lay = wl.make_layout(lens, 1, gap_max=5, shuffle=True, rng=rng)
+    w = wl.Workload(f"pfalike{hq}", 150 + hq % 40, 1, len(lens), hq, hkv, 1, "uniform", 1, 2, peaky_frac=0.05)
+    k, v = wl.layer_kv_bits(w, lay, 0, fill=wl.BF16_NAN)
+    shared = rng.choice([-1.0, 1.0], size=128).astype(np.float32)
+    for b in range(len(lens)):
+        for i, tok in enumerate((40, 205, 340, 495)):  # blocks 1, 6, 10 and 15: waves 1, 2, 2 and 3
+            if tok < lens[b]:
+                k[lay.offsets[b] + tok] = bf((0.5 + 0.25 * i) * shared)
+    qs = np.concatenate([[0], np.cumsum(nq)[:-1]]).astype(np.int32)
+    q = bf(rng.standard_normal((int(nq.sum()), hq, 128)).astype(np.float32) + shared)
+    outs = through_each_kind(w, lay, lens, nq, qs, q, k, v)
+    used = np.concatenate([np.arange(o, o + n) for o, n in zip(lay.offsets, lens)])
+    vmax = float(np.abs(wl.bf16_bits_to_f32(v[used])).max())
+    over = []
+    for b in range(len(lens)):
+        rows = slice(int(qs[b]), int(qs[b] + nq[b]))
+        diff = float(np.abs(outs["narrow"][rows] - outs["wide"][rows]).max())
+        bound = 4 * 32 * -(-int(lens[b]) // 32) * 2.0**-24 * vmax
+        print(f"{hq}/{hkv} {lens[b]} tokens: narrow and wide differ by {diff:.2e} (bound {bound:.2e})", flush=True)
+        over += [int(lens[b])] if diff > bound else []
+    assert not over, f"contexts of {over} tokens"
+
+
+@pytest.mark.parametrize("split_p", MODES)
+def test_prefill_narrow_long_context(split_p):
+    """The call that the narrow workgroups are for: one request, 300 new tokens over
+    9,000 with peaky keys, plus keys along a component that all queries share, one in
+    each wave's blocks with rising logits (the sums of every wave are rescaled for
+    blocks of the others).  Against the oracle: within the rounding bound of the bf16
+    weights (test_prefill_bf16_weights_worst_case_against_the_rounding_bound), or to
+    fp32 rounding with the two-term ones."""
+    hq, hkv, hist, new = 32, 8, 9000, 300
+    rng = np.random.default_rng(91)
+    w = wl.Workload("pflong", 189, 1, 1, hq, hkv, 1, "uniform", 1, 2, peaky_frac=0.05)
+    n = hist + new
+    lay = wl.make_layout(np.array([n], np.int32), 1)
+    k, v = wl.layer_kv_bits(w, lay, 0)
+    off = int(lay.offsets[0])
+    shared = rng.choice([-1.0, 1.0], size=128).astype(np.float32)
+    for i, block in enumerate((40, 97, 150, 211)):  # waves 0, 1, 2 and 3
+        k[off + 32 * block + 7] = bf((0.5 + 0.25 * i) * shared)
+    q = bf(rng.standard_normal((new, hq, 128)).astype(np.float32) + shared)
+    zero, dn = up_i32(np.zeros(1, np.int32)), up_i32(np.array([n], np.int32))
+    out = torch.empty(q.shape, dtype=torch.float32, device=dev())
+    with DecodeAttention(hq, hkv, 1, 16384) as attn:
+        attn.prefill(up_bf16(q), up_bf16(k), up_bf16(v), up_i32(lay.offsets), dn, zero,
+                     up_i32(np.array([new], np.int32)), new, w.scale, out, split_p=split_p)
+        torch.cuda.synchronize()
+    sel = [0, 11, 12, 150, new - 1]
+    offs, plen = np.full(len(sel), off, np.int32), np.array([hist + r + 1 for r in sel], np.int32)
+    got, qh = out.cpu().numpy()[sel].astype(np.float64), q[sel]
+    ref = oracle.decode_attn(qh, k, v, offs, plen, w.scale)
+    assert_parity(got, ref, f"one long request split_p={split_p}", tight=split_p)
+    if not split_p:
+        bound = np.stack([2 * U_BF16 / (1 - U_BF16)
+                          * weighted_deviation(qh[r], h, k, v, off, int(plen[r]), w.scale, h // 4, ref[r, h])
+                          for r in range(len(sel)) for h in range(hq)]).reshape(ref.shape) + 1e-4
+        err = np.abs(got - ref)
+        assert (err <= bound).all(), f"above the bf16-weight rounding bound at {np.argwhere(err > bound)[:5]}"
