@@ -364,6 +364,42 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
     __builtin_amdgcn_s_setprio(0);
   };
+  // a staged block after those before it
+  auto attend = [&](int t0, const uint16_t* kt, const uint16_t* vt) __attribute__((always_inline)) {
+    f32x4 sc[kTiles][2];
+    u32x4 phi[kTiles], plo[kTiles];
+    float lm[kTiles];
+    scores(kt, sc);
+    // lazy rescale: the column maxima are taken only then
+    if (maxima(t0, sc, lm)) {
+      const bool masked = is_masked(t0);
+#pragma unroll
+      for (int ct = 0; ct < kTiles; ++ct) {
+        // A tile whose own logits stay below its thresholds keeps its maxima: a
+        // row's weights are rounded as they would be without the other tiles'
+        // rows (and rescaling all three took 10.09 ms against 10.03 for the burst).
+        const float t1 = thr[ct], t2 = thr_raw[ct];
+        if (!__any(lm[ct] > (masked ? t1 : t2))) continue;
+        rescale(ct, fmaxf(st[ct].m, column_max(lm[ct] * (masked ? 1.f : cs))), false);
+      }
+    }
+    weights(t0, sc, phi, plo);
+    values(vt, phi, plo);
+  };
+  // the wave's output rows, where it has seen all of their tokens
+  auto finish = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ct = 0; ct < kTiles; ++ct) {
+      float l_tot = st[ct].l + __shfl_xor(st[ct].l, 16);
+      l_tot += __shfl_xor(l_tot, 32);
+      if (qi[ct] < nq) {
+        const float inv = 1.0f / l_tot;
+        OutT* orow = out + ((size_t)(q_starts[b] + qi[ct]) * pp.hq + (size_t)kv * g + hh[ct]) * kHeadDim + 4 * c;
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) store4<OutT>(orow + 16 * nb, o[ct][nb] * inv);
+      }
+    }
+  };
   if constexpr (!kSplitKv) {
     __shared__ __attribute__((aligned(16))) uint16_t lds_k1[kStageElems];
     __shared__ __attribute__((aligned(16))) uint16_t lds_v1[kStageElems];
@@ -390,27 +426,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       __builtin_amdgcn_s_waitcnt(kWaitBlock);
       lds_barrier();
       issue(t0 + 2 * kPrefillBlock, nk, nv);
-      if (wave_active && t0 < wave_end) {
-        f32x4 sc[kTiles][2];
-        u32x4 phi[kTiles], plo[kTiles];
-        float lm[kTiles];
-        scores(kt, sc);
-        // lazy rescale: the column maxima are taken only then
-        if (maxima(t0, sc, lm)) {
-          const bool masked = is_masked(t0);
-#pragma unroll
-          for (int ct = 0; ct < kTiles; ++ct) {
-            // A tile whose own logits stay below its thresholds keeps its maxima: a
-            // row's weights are rounded as they would be without the other tiles'
-            // rows (and rescaling all three took 10.09 ms against 10.03 for the burst).
-            const float t1 = thr[ct], t2 = thr_raw[ct];
-            if (!__any(lm[ct] > (masked ? t1 : t2))) continue;
-            rescale(ct, fmaxf(st[ct].m, column_max(lm[ct] * (masked ? 1.f : cs))), false);
-          }
-        }
-        weights(t0, sc, phi, plo);
-        values(vt, phi, plo);
-      }
+      if (wave_active && t0 < wave_end) attend(t0, kt, vt);
     };
     issue(0, lds_k0, lds_v0);
     issue(kPrefillBlock, lds_k1, lds_v1);
@@ -441,18 +457,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
     // no load may land in LDS after the workgroup has released it
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
-
-#pragma unroll
-    for (int ct = 0; ct < kTiles; ++ct) {
-      float l_tot = st[ct].l + __shfl_xor(st[ct].l, 16);
-      l_tot += __shfl_xor(l_tot, 32);
-      if (qi[ct] < nq) {
-        const float inv = 1.0f / l_tot;
-        OutT* orow = out + ((size_t)(q_starts[b] + qi[ct]) * pp.hq + (size_t)kv * g + hh[ct]) * kHeadDim + 4 * c;
-#pragma unroll
-        for (int nb = 0; nb < 8; ++nb) store4<OutT>(orow + 16 * nb, o[ct][nb] * inv);
-      }
-    }
+    finish();
   } else {
     // Wave w takes blocks w, w + 4, w + 8, ... of the workgroup's token range
     // through its own K and V tiles.  A tile is refilled with the wave's next
@@ -481,6 +486,39 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 #pragma unroll
       for (int r = 0; r < kLoads; ++r) load16_to_lds(rs, lds_row(dst, r), dvo[r]);
     };
+    // Contexts of up to kAlone blocks are one wave's, in order, without the exchange
+    // and the merge; the tiles hold its next four blocks.  A prompt of 12 tokens 6.1
+    // us, shared by the waves 9.0 (wide 6.0); 12 tokens over 140 9.5 and 10.2.  With
+    // a limit of 8, 12 over 240 11.9 against 10.1.
+    constexpr int kAlone = 6;
+    if (kv_end <= kAlone * kPrefillBlock) {
+      if (wave > 0) return;
+      auto fill = [&](int t0, int slot) {
+        issue(kseq, t0, lds_k0 + slot * kBlockElems);
+        issue(vseq, t0, lds_v0 + slot * kBlockElems);
+      };
+      for (int t0 = 0; t0 < kv_end && t0 < kStride; t0 += kPrefillBlock) fill(t0, t0 / kPrefillBlock);
+#pragma nounroll
+      for (int t0 = 0; t0 < kv_end; t0 += kPrefillBlock) {
+        const int slot = t0 / kPrefillBlock % kPrefillWaves;
+        // all loads have landed but those of the blocks after this one
+        if (t0 + 3 * kPrefillBlock < kv_end)
+          __builtin_amdgcn_s_waitcnt(wait_vmcnt(3 * 2 * kLoads));
+        else if (t0 + 2 * kPrefillBlock < kv_end)
+          __builtin_amdgcn_s_waitcnt(wait_vmcnt(2 * 2 * kLoads));
+        else if (t0 + kPrefillBlock < kv_end)
+          __builtin_amdgcn_s_waitcnt(wait_vmcnt(2 * kLoads));
+        else
+          __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+        asm volatile("" ::: "memory");
+        attend(t0, lds_k0 + slot * kBlockElems, lds_v0 + slot * kBlockElems);
+        // the tiles' reads have returned before their refill is issued
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (t0 + kStride < kv_end) fill(t0 + kStride, slot);
+      }
+      finish();
+      return;
+    }
     // What the blocks before blk have published, one per lane, 0 past them.  Plain
     // accesses between compiler fences: before an atomic one the compiler waits for
     // all loads into LDS, the tiles' among them.
