@@ -205,7 +205,11 @@ int ctx_decode_attn_run_paged(ctx_decode_attn* handle, const void* q, void* k_pa
  *                absolute) at half again the matrix-core work.
  *   out          [total_q, Hq, D] of desc.out_dtype; rows of no sequence are untouched
  * Any group size the handle accepts (Hq / Hkv <= 16).  No workspace, no
- * allocation, no host sync; deterministic.
+ * allocation, no host sync; deterministic for a given call.  num_seqs, max_q_len,
+ * the head counts, desc.max_seq_len and the device's CU count choose between two
+ * ways of sharing the work out.  Both round a row's softmax weights alike, but they
+ * add in another order: the same request alone and in a batch may differ by fp32
+ * rounding (about 1e-6), and then in the last bit of a bf16 output.
  * Errors: INVALID_ARG (also for unknown flag bits), CAPACITY, ALIGNMENT, HIP.
  */
 #define CTX_PREFILL_SPLIT_P 1u

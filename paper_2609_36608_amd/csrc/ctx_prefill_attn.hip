@@ -723,21 +723,26 @@ extern "C" int ctx_prefill_attn_run(ctx_decode_attn* h, const void* q, const voi
   const int64_t cols = (int64_t)max_q_len * g;
   const int64_t units = round_up(pp.units, kXcds);  // padded to whole XCD rounds
   const int64_t whole = units * ((cols + kPrefillCols - 1) / kPrefillCols);
-  // A CU holds two workgroups of either kind.  As long as the narrow ones (4
-  // times as many, each through a quarter of the tokens) are all resident at
-  // once, they finish first at any context length: one request with 301 new
-  // tokens over 8,000 (208 narrow workgroups) 65 us against 219, with 60 over 600
-  // 11.5 and 20.9.  In a second round each pays its start and its merge again,
-  // which only long contexts win back, and their length is not known here: 4
-  // requests over 4,096..12,288 tokens 237 against 342 us, but 8 fresh prompts of
-  // 300 tokens 40 against 22.5, 30 requests with 60..90 over 1,200 64 against 46.
-  // One per CU is the limit where they are no more than the wide ones (64 requests
-  // with up to 12 new tokens each 33.0 against 32.1 us), or where the handle's
-  // bound says that no wave can have three blocks (32 requests over up to 148
-  // tokens 13.5 against 12.2 us).
+  // A CU holds two workgroups of either kind.  As long as the narrow ones (up to 4
+  // times as many, each wave through a quarter of the tokens) are all resident at
+  // once, they finish first but for the shortest contexts: one request with 301 new
+  // tokens over 8,000 (208 narrow workgroups) 81 us against 212, with 60 over 600
+  // 14.4 and 22.5; two fresh prompts of 301 15.0 and 14.1.  In a second round each
+  // pays its start and its merge again, which only long contexts win back, and
+  // their length is not known here: 4 requests over 4,096..12,288 tokens 222 against
+  // 286 us, but 8 fresh prompts of 300 tokens 40.7 against 21.7, 30 requests with
+  // 60..90 over 1,200 97 against 58.
+  // The fewer waves of the wide ones are idle, the less there is to win.  Where the
+  // narrow ones are no more than the wide, one per CU is the limit (64 requests with
+  // up to 12 new tokens over up to 400 19.2 against 17.5 us); where they are twice as
+  // many, three for two CUs (13..16 new tokens over 2,000: 24 requests 46 against 53
+  // us, 28 51 and 53, 32 63 and 54; over 300 28 requests 18.2 and 15.6, 32 18.7 and
+  // 15.7); one per CU also where the handle's bound says that no wave can have three
+  // blocks (16 requests with 30..36 over up to 220 14.1 against 12.8).
   const int64_t narrow = units * ((cols + kSplitCols - 1) / kSplitCols);
-  const int per_cu = narrow == whole || d.max_seq_len <= 2 * kPrefillWaves * kPrefillBlock ? 1 : 2;
-  const bool split_kv = narrow <= per_cu * (int64_t)h->num_cus;
+  const bool one_per_cu = narrow <= whole || d.max_seq_len <= 2 * kPrefillWaves * kPrefillBlock;
+  const int per_two_cus = one_per_cu ? 2 : narrow <= 2 * whole ? 3 : 4;
+  const bool split_kv = 2 * narrow <= per_two_cus * (int64_t)h->num_cus;
   // up to 16 blocks at most: the last two steps of the wide kernel's loop count
   const bool short_kv = d.max_seq_len <= 16 * kPrefillBlock;
   const int64_t blocks = split_kv ? narrow : whole;
