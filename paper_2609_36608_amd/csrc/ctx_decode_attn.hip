@@ -55,16 +55,24 @@ constexpr int kMaxGroup = 16;     // query heads per KV head (MFMA N dimension)
 // dependent loads, so one block per wave beats fewer, longer ranges (same merge
 // for all three): a step of 28 layers over 4 contexts of 256..1024 tokens 399,
 // 419 and 472 us with 16, 32 and 64; one context of 1,000 tokens 11.2, 12.2 and
-// 13.9 us.  Larger batches have longer ranges anyway.
+// 13.9 us.  Larger batches have longer ranges anyway, but with few KV heads only much
+// larger ones, and there the partials (one output row per query head of the group and
+// range) come to cost more than the tokens: 16/1 heads, 16 contexts of 500..5,000
+// tokens 24.9, 18.6 and 15.6 us, one of 4,000 11.1, 9.6 and 9.7; 32/4 heads, 8 of
+// 500..2,000 17.5, 14.4 and 14.2; 12/2 heads, 8 of 500..2,000 12.5, 11.6 and 12.5.  So
+// the smallest range is 32 tokens from kWideRows partial rows per KV head on (in
+// ranges of 16), and 64 from kWidestRows on (in ranges of 32).
 constexpr int kMinRange = 16;
+constexpr int kWideRows = 2560;
+constexpr int kWidestRows = 5120;
 // waves of a merge workgroup in which seg_waves waves share a head's segments
 constexpr int merge_waves(int seg_waves) { return seg_waves < 4 ? 4 : seg_waves; }
 constexpr int kWgWaves = 8;  // most waves (KV heads of one range) per split workgroup
 constexpr int kTileBytes = 2 * kBlock * kHeadDim * 2;  // one wave's K and V tiles in LDS
-// Waves per SIMD the split kernel is compiled for: 3 for contiguous caches
-// (167 VGPRs); the paged kernel's page bookkeeping needs more registers and
-// spills at 3, so it is compiled for 2.  An 8-wave workgroup (Hkv = 8) is one
-// workgroup per CU either way.
+// Waves per SIMD the split kernel is compiled for: 3 for contiguous caches (159
+// VGPRs), 2 for paged ones (168, which a third wave would just fit: it is the slower
+// choice, see resident_waves).  An 8-wave workgroup (Hkv = 8) is one workgroup per
+// CU either way.
 constexpr int kWavesPerEu = 3;
 constexpr int kPagedWavesPerEu = 2;
 
@@ -75,6 +83,8 @@ struct Plan {
   int32_t group;
   int32_t num_ranges;    // ranges in the grid (each = hkv workgroups)
   int32_t forced_width;  // > 0: fixed tokens per range
+  int32_t wide_from;     // most tokens of a batch in ranges of kMinRange, and of twice that
+  int32_t widest_from;
   int32_t pad;           // sequences occupy round_up(L, pad) tokens of the flattened batch
   float scale_log2;      // scale * log2(e)
 };
@@ -186,7 +196,8 @@ __device__ __forceinline__ int64_t range_width(int64_t total, const Plan& p) {
   if (p.forced_width > 0) return p.forced_width;
   int64_t w = (total + p.num_ranges - 1) / p.num_ranges;
   w = (w + kBlock - 1) / kBlock * kBlock;
-  return w < kMinRange ? kMinRange : w;
+  const int least = total > p.widest_from ? 4 * kMinRange : total > p.wide_from ? 2 * kMinRange : kMinRange;
+  return w < least ? least : w;
 }
 
 // ------------------------------------------------------------ math helpers
@@ -793,6 +804,8 @@ int launch(ctx_decode_attn* h, const void* q, const void* k, const void* v, cons
                      ? (int32_t)round_up(((int64_t)num_seqs * round_up(d.max_seq_len, kPaged ? kBlock : 1) +
                                           d.split_tokens - 1) / d.split_tokens, kXcds)
                      : h->ranges_auto[kPaged ? 1 : 0];
+  p.wide_from = kWideRows * kMinRange / p.group;
+  p.widest_from = kWidestRows * 2 * kMinRange / p.group;
   p.pad = kPaged ? kBlock : 1;
   p.scale_log2 = (float)((double)scale * 1.4426950408889634);
 

@@ -360,3 +360,23 @@ def test_merge_segment_counts(hq, hkv, segments):
     # bf16 rounds the same fp32 values to nearest: half an ulp is at most 2^-8 of the value
     got = run(hq, hkv, q, k, v, lay.offsets, lens, w.scale, out_dtype=torch.bfloat16, canary=True)
     assert (np.abs(got - ref) <= 2.0**-8 * np.abs(ref) + 2e-4).all(), what
+
+
+@pytest.mark.parametrize("hq,hkv", [(16, 1), (32, 4), (14, 2), (12, 2)])
+def test_smallest_range_grows_with_the_partial_rows(hq, hkv):
+    """The smallest balanced range is 16, 32 or 64 tokens by the partial rows that a KV
+    head would write: just up to and just past each line the result is bit for bit
+    that of a split into ranges of that length, and within rounding of the oracle."""
+    g = hq // hkv
+    rng = np.random.default_rng(hq + hkv)
+    w = wl.Workload("minrange", 161, 1, 1, hq, hkv, 1, "uniform", 1, 2)
+    for line, below, above in ((2560 * 16 // g, 16, 32), (5120 * 32 // g, 32, 64)):
+        for n, width in ((line, below), (line + 1, above)):
+            lens = np.array([n], np.int32)
+            lay = wl.make_layout(lens, 1)
+            q = rand_bits(rng, (1, hq, 128))
+            k, v = rand_bits(rng, (lay.num_rows, hkv, 128), 3.0), rand_bits(rng, (lay.num_rows, hkv, 128))
+            got = run(hq, hkv, q, k, v, lay.offsets, lens, w.scale, canary=True)
+            assert_parity(got, oracle.decode_attn(q, k, v, lay.offsets, lens, w.scale), f"{hq}/{hkv} {n} tokens")
+            forced = run(hq, hkv, q, k, v, lay.offsets, lens, w.scale, split_tokens=width)
+            np.testing.assert_array_equal(got, forced, err_msg=f"{hq}/{hkv}: {n} tokens not in ranges of {width}")
