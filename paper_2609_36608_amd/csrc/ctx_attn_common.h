@@ -114,19 +114,6 @@ __device__ __forceinline__ void store4<uint16_t>(uint16_t* dst, f32x4 v) {
   *reinterpret_cast<u32x2*>(dst) = u;
 }
 
-template <typename OutT>
-__device__ __forceinline__ void store2(OutT* dst, float a, float b);
-
-template <>
-__device__ __forceinline__ void store2<float>(float* dst, float a, float b) {
-  *reinterpret_cast<float2*>(dst) = make_float2(a, b);
-}
-
-template <>
-__device__ __forceinline__ void store2<uint16_t>(uint16_t* dst, float a, float b) {
-  *reinterpret_cast<uint32_t*>(dst) = pack_bf16x2(a, b);
-}
-
 // ------------------------------------------------------------ host helpers
 
 int fail(int code, const char* fmt, ...) {

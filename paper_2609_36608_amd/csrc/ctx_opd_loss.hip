@@ -15,8 +15,8 @@
 //   * opd_row_kernel: persistent workgroups walk the token rows; each holds a
 //     whole row in registers (thread t owns the 16-byte chunks t + kThreads k,
 //     k < C: coalesced, non-temporal loads) and has 256, 512 or 1024 threads, the
-//     fewest that can (up to 19 chunks per thread; 26 of 512 threads), so that a CU works on 4, 2 or
-//     1 rows (8 short ones) at different stages.  It reduces the row maximum and
+//     fewest that can (up to 19 chunks per thread; 26 of 512 threads), so that a CU
+//     works on 4, 2 or 1 rows (8 short ones) at different stages.  It reduces the row maximum and
 //     the sum of exp over the registers (lane moves, then the waves' partials
 //     through LDS, always in the same order), forms lp, the clipped ratio, the
 //     dual-clip loss and the per-row gradient scale g, and writes the gradient
@@ -25,7 +25,8 @@
 //     second exp pass; a masked row is not read at all.  The next row's loads are
 //     issued chunk by chunk as the last pass frees the registers: the gradient
 //     pass, or for the loss alone the sum pass (5,716 rows of 151,936 columns:
-//     355 us when it waited for the row's end, 288 now, 5.97 TB/s).
+//     355 us when it waited for the row's end, 288 then, 271 with row_max's packed
+//     words, 6.35 TB/s).
 //   * opd_reduce_kernel: loss = sum_j w_j l_j in double precision, one
 //     workgroup, fixed order (deterministic, no atomics).
 
@@ -536,7 +537,11 @@ extern "C" int ctx_opd_loss_run(const void* logits, int64_t row_stride, int32_t 
     // columns 90 and 133 us, 32,000 130 and 153 (512 threads: 139), the loss alone
     // 61 and 69; 50,257 columns with 512 threads 229 and 242, 100,277 (25 chunks
     // per thread) 466 and 476, alone 179 and 193.  With 256 threads 20 to 26
-    // chunks gain nothing: 45,000 columns 206 and (512 threads) 203.
+    // chunks gain nothing: 45,000 columns 206 and (512 threads) 203.  Those are
+    // batches of thousands of rows; with fewer rows than CUs, where a row is alone on
+    // its CU, the fewer waves lose nothing either: against 1024 threads 16 rows of
+    // 32,000 columns 9.3 and 10.8 us with the gradient, 100 of 50,257 14.0 and 14.8,
+    // 256 of 100,277 29.9 and 29.3 (the loss alone 19.4 and 20.0).
     if (per_thread(256) <= kMaxChunksPerThread)
       launch_rows_of<256, 1, kMaxChunksPerThread>(per_thread(256), a);
     else if (per_thread(512) <= kMaxChunks512)
