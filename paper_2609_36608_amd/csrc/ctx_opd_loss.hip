@@ -65,7 +65,8 @@ constexpr int kLightChunks = 4;
 // Calls of up to kOwnWeightTokens tokens whose rows take 256 threads find each
 // row's weight in the row kernel, which saves the launch of opd_weight_kernel (a
 // small call is bound by its launches) for at most one read of the mask, 2 KiB
-// from L2, per row.  Longer rows keep the launch: the work would take them past
+// from L2, and of as many response bounds per row; with more responses than that,
+// most of them empty, the search would grow past it.  Longer rows keep the launch: the work would take them past
 // the registers that let two workgroups share a CU.
 constexpr int32_t kOwnWeightTokens = 2048;
 constexpr int kOwnWeightThreads = 256;
@@ -524,7 +525,8 @@ extern "C" int ctx_opd_loss_run(const void* logits, int64_t row_stride, int32_t 
     if (e != hipSuccess) return fail(CTX_ERR_HIP, "device query: %s", hipGetErrorString(e));
     const int chunks = (vocab + kChunk - 1) / kChunk;
     const auto per_thread = [&](int threads) { return (chunks + threads - 1) / threads; };
-    const bool own = num_tokens <= kOwnWeightTokens && per_thread(kOwnWeightThreads) <= kMaxChunksPerThread;
+    const bool own =
+        num_tokens <= kOwnWeightTokens && num_seqs <= kOwnWeightTokens && per_thread(kOwnWeightThreads) <= kMaxChunksPerThread;
     if (!own)
       hipLaunchKernelGGL(opd_weight_kernel, dim3((unsigned)num_seqs), dim3(256), 0, s, mask, seq_starts, num_seqs,
                          p.eps, token_weight);

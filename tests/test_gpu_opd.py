@@ -333,3 +333,20 @@ def test_opd_abi_errors():
     torch.cuda.synchronize()
     assert float(loss.cpu()[0]) == 0.0
     assert bd.load_library().ctx_decode_attn_last_error() is not None
+
+
+@pytest.mark.parametrize("responses", [2048, 2049, 20000])
+def test_opd_more_responses_than_tokens(responses):
+    """Response counts on both sides of the one up to which the row kernel looks for
+    a row's response, nearly all of them empty: the weights are exact to fp32
+    rounding of 1 / (B (M + eps)) either way."""
+    rng = np.random.default_rng(responses)
+    n, vocab = 333, 17
+    starts = np.sort(np.concatenate([[0], rng.integers(0, n + 1, responses - 1), [n]])).astype(np.int32)
+    z = wl.f32_to_bf16_bits(rng.standard_normal((n, 24)).astype(np.float32))
+    old = (-rng.exponential(1.0, n)).astype(np.float32)
+    b = wl.OpdBatch(starts, rng.integers(0, vocab, n).astype(np.int32), (rng.random(n) > 0.4).astype(np.uint8),
+                    np.zeros(n), old, (old + rng.normal(0, 1, n)).astype(np.float32))
+    ref = oracle.opd_loss(z[:, :vocab], b.tokens, b.old_lp, b.teacher_lp, b.mask, b.seq_starts)
+    for grad in (True, False):
+        check_scalars(run_gpu(up_bf16(z), b, vocab, grad=grad), ref, b, f"{responses} responses")
